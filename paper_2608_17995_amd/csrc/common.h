@@ -170,6 +170,15 @@ __device__ __forceinline__ void buffer_load16(u32x4& dst, const u32x4& rsrc, uin
   asm volatile("buffer_load_dwordx4 %0, %1, %2, 0 offen" : "=v"(dst) : "v"(voff), "s"(rsrc) : "memory");
 }
 
+// 16-byte-per-lane buffer load that lands in LDS directly: lane l's data goes
+// to LDS byte dst + off + 16 l (dst + off wave-uniform).  No register receives the
+// data; completion is counted by vmcnt like any load.
+__device__ __forceinline__ void lds_load16(uint32_t dst, uint32_t voff, const u32x4& rsrc, uint32_t soff,
+                                           uint32_t off = 0) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               ::"s"(dst + off), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+}
+
 // Wait until at most N vector-memory operations of this wave are in flight
 // (they complete in issue order).
 template <int N>

@@ -10,11 +10,13 @@
 //    the workgroup alternate compute and memory phases.
 //  - The MFMA computes C^T = W A^T, so each lane owns groups of four
 //    consecutive output columns of one row (8-byte stores in the epilogue).
-//  - k-tiles are staged global -> registers -> LDS through two LDS buffers,
-//    one barrier per k-tile: while tile t is multiplied, tile t+1 is in
-//    flight (and, for the 128-wide tile, tile t+2 too).  LDS rows are 128 bytes (64 bf16) with the 16-byte chunk index
-//    XOR-swizzled by (row / 2) mod 8, which makes both the staging writes and
-//    the 16-byte fragment reads of 16 consecutive rows bank-conflict free.
+//  - k-tiles are staged global -> LDS: directly in the ping-pong kernel, through
+//    registers and two LDS buffers in the narrower ones (one barrier per
+//    k-tile: while tile t is multiplied, tile t+1 is in flight and, for the
+//    128-wide tile, tile t+2 too).  LDS rows are 128 bytes (64 bf16) with the
+//    16-byte chunk index XOR-swizzled by (row / 2) mod 8, which makes both the
+//    staging writes and the 16-byte fragment reads of 16 consecutive rows
+//    bank-conflict free.
 //  - The epilogue goes through LDS wave by wave so that every store covers
 //    whole row segments (or, for the transposed store, column runs).
 //  - Small-N GEMMs (the N = D projections) are split along K when the tile
@@ -29,6 +31,8 @@
 // fp32 path: 64x64 tiles on the VALU (the exactness path).
 #include <stdio.h>
 #include <stdlib.h>
+
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -286,11 +290,6 @@ __device__ __forceinline__ bool decode_tile(const GemmArgs& a, int bm, int bn, i
   return m0 < a.p[prob].M && n0 < a.N;
 }
 
-__device__ __forceinline__ int64_t tiles_total(const GemmArgs& a, int bm, int bn) {
-  const int64_t tn = (a.N + bn - 1) / bn;
-  return ((a.p[0].M + bm - 1) / bm + (a.nprob > 1 ? (a.p[1].M + bm - 1) / bm : 0)) * tn;
-}
-
 // Workgroup -> (problem, tile origin, k split): the k splits of a tile are
 // adjacent logical ids.
 __device__ __forceinline__ bool map_tile(const GemmArgs& a, int bm, int bn, int splits, int& prob, int64_t& m0,
@@ -298,28 +297,6 @@ __device__ __forceinline__ bool map_tile(const GemmArgs& a, int bm, int bn, int 
   const int64_t bid = xcd_logical_id(blockIdx.x, gridDim.x);
   ks = int(bid % splits);
   return decode_tile(a, bm, bn, bid / splits, prob, m0, n0);
-}
-
-// Split tail.  When the tiles overrun the last full wave of workgroups on the
-// chip by a few, the first F = tiles - tail tiles run whole (workgroups
-// 0 .. F - 1) and the last `tail` tiles run in `tsp` k splits each
-// (workgroups F onwards, dispatched after the whole tiles): the partial wave
-// takes 1 / tsp of a tile's time instead of a whole one.  The two classes are
-// renumbered for the XCDs separately.  tidx is the tile's index in the tail
-// (-1 for a whole tile).
-__device__ __forceinline__ bool map_tile_tail(const GemmArgs& a, int bm, int bn, int64_t tail, int tsp, int& prob,
-                                              int64_t& m0, int64_t& n0, int& ks, int64_t& tidx) {
-  const int64_t F = tiles_total(a, bm, bn) - tail;
-  const int64_t bid = blockIdx.x;
-  if (bid < F) {
-    ks = 0;
-    tidx = -1;
-    return decode_tile(a, bm, bn, xcd_logical_id(bid, F), prob, m0, n0);
-  }
-  const int64_t u = xcd_logical_id(bid - F, int64_t(gridDim.x) - F);
-  tidx = u / tsp;
-  ks = int(u % tsp);
-  return decode_tile(a, bm, bn, F + tidx, prob, m0, n0);
 }
 
 // Epilogue through LDS, wave by wave.  The MFMA layout gives each lane four
@@ -639,79 +616,354 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(const
                                   reinterpret_cast<float*>(&lds[0][0]), wave, wm, wn, lane);
 }
 
+// Epilogue of the ping-pong kernel: each wave turns its 128 x 64 block around
+// in its own 16 KB of LDS, as bf16 results (bias, GELU and the gated residual
+// are applied on the accumulators), so one 16-byte store instruction covers
+// 8 rows of 128 bytes, or 4 columns of 256 bytes in a transposed region.  A
+// wave's LDS operations complete in order: no barrier.  The caller passes the
+// main loop's LDS once every wave is done with it.
+//   acc[i][j][4q + r] = C[row 32 i + l32][col 32 j + 8 q + 4 hi + r].
+// Row-major image: 128-byte rows, 16-byte chunk c of row r at chunk
+// c ^ ((r / 2) mod 8), its 8-byte halves exchanged when bit 4 of r is set:
+// the 8-byte accumulator writes (32 rows, one chunk) and the 16-byte row
+// reads are free of bank conflicts.
+// Transposed image: 256-byte columns; lanes l, l ^ 1 first exchange half of
+// their four columns, so each holds two rows of two columns and writes
+// 4-byte row pairs; 16-byte chunk k of column c is at k ^ 4 ((c / 2) mod 4).
+// Split-K partials are stored as fp32 straight from the accumulators.
+// Every global access is a buffer access whose range (or an offset past it)
+// drops the rows >= M and the columns >= N: with plain accesses the bounds
+// were a branch per 16 bytes, and the epilogue took 9 us of a 252-tile launch.
+typedef const __attribute__((address_space(4))) GemmArgs* GemmArgsPtr;
+typedef const __attribute__((address_space(4))) GemmProblem* GemmProblemPtr;
+constexpr uint32_t kPast = 0x80000000u;  // a buffer offset past every range used below
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const void* base, int64_t bytes) {
+  const uint32_t n = bytes <= 0 ? 0u : bytes >= int64_t(kPast) ? kPast : uint32_t(bytes);
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, int(n), 0x00020000);
+}
+
+template <int TM, int TN>
+__device__ __forceinline__ void pp_epilogue(GemmArgsPtr a, GemmProblemPtr p, int64_t m0, int64_t n0,
+                                            float* __restrict__ pbase, int64_t pld, const f32x16 (&acc)[TM][TN],
+                                            u32x4* sm, int wave, int wm, int wn, int lane) {
+  constexpr int WM = 32 * TM, WN = 32 * TN;
+  static_assert(WM == 128 && WN == 64, "LDS image");
+  const int l32 = lane % 32, hi = lane / 32;
+  const int64_t nb = n0 + wn * WN, mb = m0 + wm * WM, M = p->M, N = a->N;
+  if (nb >= N || mb >= M) return;
+  const int rows = int(std::min<int64_t>(WM, M - mb)), cols = int(std::min<int64_t>(WN, N - nb));
+  if (pbase) {
+    const __amdgpu_buffer_rsrc_t r = buf(pbase + wm * WM * pld + wn * WN, rows * pld * 4);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const uint32_t row = uint32_t(32 * i + l32) * uint32_t(pld * 4) + 16 * hi;
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x16& c = acc[i][j];
+          const int n = 32 * j + 8 * q;  // cols is a multiple of 8 (split launches need N % 8 == 0)
+          const f32x4 w = {c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, w), r, int(n < cols ? row + 4 * n : kPast), 0,
+                                                 0);
+        }
+    }
+    return;
+  }
+  const int64_t n_split = a->n_split, n_split2 = a->n_split2;
+  const bool r0 = nb < n_split, r1 = nb < n_split2;
+  const int mode = r0 ? a->mode0 : r1 ? a->mode1 : a->mode2;
+  bf16_t* out = static_cast<bf16_t*>(r0 ? p->out0 : r1 ? p->out1 : p->out2);
+  const int64_t ldo = r0 ? p->ld0 : r1 ? p->ld1 : p->ld2;
+  const int64_t col0 = nb - (r0 ? 0 : r1 ? n_split : n_split2);
+  // This lane's columns 32 j + 8 q + 4 hi .. + 3 of the strip (zeros past N).
+  auto load4 = [&](const void* base, u32x2 (&dst)[TN][4]) {
+    const __amdgpu_buffer_rsrc_t r = buf(static_cast<const bf16_t*>(base) + nb, base ? cols * 2 : 0);
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        dst[j][q] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, 2 * (32 * j + 8 * q + 4 * hi), 0, 0));
+  };
+  auto f4 = [](const u32x2& w, int r) {
+    return __uint_as_float(r & 1 ? w[r >> 1] & 0xffff0000u : w[r >> 1] << 16);
+  };
+  u32x2 bias[TN][4];
+  load4(p->bias, bias);
+  char* reg = reinterpret_cast<char*>(sm) + wave * (WM * WN * 2);
+  if (mode == EPI_STORE_T) {
+    const bool odd = lane & 1;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x16& c = acc[i][j];
+          const uint32_t p01 = pack_bf2(c[4 * q] + f4(bias[j][q], 0), c[4 * q + 1] + f4(bias[j][q], 1));
+          const uint32_t p23 = pack_bf2(c[4 * q + 2] + f4(bias[j][q], 2), c[4 * q + 3] + f4(bias[j][q], 3));
+          const uint32_t got = uint32_t(
+              __builtin_amdgcn_update_dpp(0, int(odd ? p01 : p23), kDppXor1, 0xf, 0xf, false));
+          const uint32_t lo = odd ? got : p01, up = odd ? p23 : got;  // rows l & ~1 and l | 1
+          const int cc = 32 * j + 8 * q + 4 * hi + 2 * int(odd);      // columns cc, cc + 1
+          const int chunk = (4 * i + (l32 >> 3)) ^ (((cc >> 1) & 3) << 2);
+          uint32_t* d = reinterpret_cast<uint32_t*>(reg + cc * (WM * 2) + chunk * 16) + ((l32 >> 1) & 3);
+          d[0] = __builtin_amdgcn_perm(up, lo, 0x05040100u);
+          d[WM * 2 / 4] = __builtin_amdgcn_perm(up, lo, 0x07060302u);
+        }
+    const int k = lane % 16;
+    auto column = [&](int cc) {
+      return *reinterpret_cast<const u32x4*>(reg + cc * (WM * 2) + (k ^ (((cc >> 1) & 3) << 2)) * 16);
+    };
+    // Plain stores: a transposed row may start at any element.
+    bf16_t* dst = out + col0 * ldo + mb;
+    const bool whole = 8 * k + 8 <= rows;
+#pragma unroll
+    for (int it = 0; it < WN / 4; ++it) {
+      const int cc = lane / 16 + 4 * it;
+      const u32x4 w = column(cc);
+      if (whole && cc < cols) *reinterpret_cast<u32x4*>(dst + cc * ldo + 8 * k) = w;
+    }
+    if (rows % 8 != 0 && k == rows / 8) {  // the last, partial group of eight rows
+#pragma unroll 1
+      for (int cc = lane / 16; cc < cols; cc += 4) {
+        const u32x4 w = column(cc);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (8 * k + e < rows) dst[cc * ldo + 8 * k + e] = bf16_t(w[e / 2] >> (16 * (e % 2)));
+      }
+    }
+    return;
+  }
+  // Row-major: lane's 16-byte role is chunk lane % 8 of rows lane / 8 + 8 it.
+  const int ch = lane % 8;
+  auto chunk_at = [&](int row) { return reg + row * (WN * 2) + ((ch ^ ((row >> 1) & 7)) * 16); };
+  auto half_at = [&](int row, int c) {  // 8-byte half hi of chunk c
+    return reg + row * (WN * 2) + ((c ^ ((row >> 1) & 7)) * 16) + 8 * (hi ^ ((row >> 4) & 1));
+  };
+  // Rows lane / 8 + 8 it: bit 4 of the row is bit 1 of it.
+  auto halves = [](const u32x4& w, int it) { return it & 2 ? u32x4{w[2], w[3], w[0], w[1]} : w; };
+  const bool col_ok = 8 * ch < cols;
+  u32x2 gate[TN][4] = {};
+  if (mode == EPI_RESID_GATE) {
+    // The residual goes through the same image, to meet the accumulators.
+    load4(p->gate, gate);
+    const int64_t ldr = p->ldr;
+    const __amdgpu_buffer_rsrc_t r = buf(static_cast<const bf16_t*>(p->resid) + mb * ldr + col0,
+                                         ((rows - 1) * ldr + cols) * 2);
+    const uint32_t off = uint32_t(lane / 8) * uint32_t(ldr * 2) + 16 * ch;
+    u32x4 res[WM / 8];
+#pragma unroll
+    for (int it = 0; it < WM / 8; ++it)
+      res[it] = __builtin_bit_cast(
+          u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, int(col_ok ? off + it * uint32_t(ldr * 16) : kPast), 0, 0));
+#pragma unroll
+    for (int it = 0; it < WM / 8; ++it) *reinterpret_cast<u32x4*>(chunk_at(lane / 8 + 8 * it)) = halves(res[it], it);
+  }
+  auto convert = [&](auto mode_tag) {
+    constexpr int kMode = decltype(mode_tag)::value;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x16& c = acc[i][j];
+          u32x2* d = reinterpret_cast<u32x2*>(half_at(32 * i + l32, 4 * j + q));
+          u32x2 rw;
+          if constexpr (kMode == EPI_RESID_GATE) rw = *d;
+          float v[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            v[r] = c[4 * q + r] + f4(bias[j][q], r);
+            if constexpr (kMode == EPI_GELU) v[r] = gelu_fast(v[r]);
+            if constexpr (kMode == EPI_RESID_GATE) v[r] = f4(rw, r) + f4(gate[j][q], r) * v[r];
+          }
+          *d = u32x2{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])};
+        }
+  };
+  if (mode == EPI_GELU) convert(std::integral_constant<int, EPI_GELU>());
+  else if (mode == EPI_RESID_GATE) convert(std::integral_constant<int, EPI_RESID_GATE>());
+  else convert(std::integral_constant<int, EPI_STORE>());
+  const __amdgpu_buffer_rsrc_t r = buf(out + mb * ldo + col0, ((rows - 1) * ldo + cols) * 2);
+  const uint32_t off = uint32_t(lane / 8) * uint32_t(ldo * 2) + 16 * ch;
+#pragma unroll
+  for (int it = 0; it < WM / 8; ++it) {
+    const u32x4 w = halves(*reinterpret_cast<const u32x4*>(chunk_at(lane / 8 + 8 * it)), it);
+    __builtin_amdgcn_raw_buffer_store_b128(w, r, int(col_ok ? off + it * uint32_t(ldo * 16) : kPast), 0, 0);
+  }
+  bf16_t* scat = static_cast<bf16_t*>(p->scat);
+  if (r0 && scat) {  // the fused scatter: selected rows also go to their canvas rows
+    const int64_t row0 = p->scat_row0, scat_n = p->scat_n, sld = p->scat_ld;
+    const int32_t* sidx = p->scat_idx;
+    int64_t at[WM / 8];
+#pragma unroll
+    for (int it = 0; it < WM / 8; ++it) {
+      const int row = lane / 8 + 8 * it;
+      const int64_t m = mb + row;
+      at[it] = row < rows && m >= row0 && col_ok ? int64_t(sidx[m - row0]) : -1;
+    }
+#pragma unroll
+    for (int it = 0; it < WM / 8; ++it) {
+      const u32x4 w = halves(*reinterpret_cast<const u32x4*>(chunk_at(lane / 8 + 8 * it)), it);
+      if (at[it] >= 0 && at[it] < scat_n) *reinterpret_cast<u32x4*>(scat + at[it] * sld + col0 + 8 * ch) = w;
+    }
+  }
+}
+
+// Tile order of the ping-pong kernel, in 32-bit arithmetic (the 64-bit
+// divisions of the general mapping cost about 1 us at the head of every
+// workgroup).  Tiles of problem 0 come first.  A problem's row tiles form
+// near-equal bands of at most kBand; a band's tiles walk down its rows, then
+// over the columns, so the 32 tiles that run on one XCD together share about
+// kBand row tiles and 4 weight tiles in its L2 (walking down all the rows
+// of a long problem re-read A once per column of tiles).
+constexpr uint32_t kBand = 8;
+struct PpTile {
+  int prob, tm, tn, ks, tidx;
+};
+__device__ __forceinline__ void pp_place(uint32_t id, uint32_t tn, uint32_t tm0, uint32_t tm1, PpTile& t) {
+  t.prob = id >= tn * tm0;
+  const uint32_t local = t.prob ? id - tn * tm0 : id, tm = t.prob ? tm1 : tm0;
+  const uint32_t bands = (tm + kBand - 1) / kBand, small = tm / bands, big = tm % bands;  // `big` bands of small + 1
+  const uint32_t in_big = big * (small + 1) * tn;
+  const bool first = local < in_big;
+  const uint32_t rows = first ? small + 1 : small, u = first ? local : local - in_big;
+  const uint32_t band = u / (rows * tn), v = u % (rows * tn);
+  t.tm = int((first ? 0 : big * (small + 1)) + band * rows + v % rows);
+  t.tn = int(v / rows);
+}
+__device__ __forceinline__ uint32_t xcd_logical_id32(uint32_t bid, uint32_t grid) {
+  const uint32_t per = grid / 8, rem = grid % 8, x = bid % 8, i = bid / 8;
+  return x * per + std::min(x, rem) + i;
+}
+// Workgroup -> tile, k split and (for a split-tail tile) its index in the
+// tail, -1 otherwise.  The k splits of a tile are adjacent ids.  Split tail:
+// when the tiles overrun the last full round of workgroups by a few, the
+// first tiles run whole and the last `tail` ones in `tsp` k splits each, in
+// the workgroups dispatched after the whole tiles: the partial round takes
+// 1 / tsp of a tile's time.  The two classes are renumbered for the XCDs
+// separately.
+__device__ __forceinline__ PpTile pp_tile(uint32_t tn, uint32_t tm0, uint32_t tm1, uint32_t splits, uint32_t tail,
+                                          uint32_t tsp) {
+  PpTile t;
+  uint32_t id;
+  const uint32_t bid = blockIdx.x, whole = tail ? tn * (tm0 + tm1) - tail : gridDim.x;
+  if (bid < whole) {
+    const uint32_t u = xcd_logical_id32(bid, whole);
+    id = u / splits;
+    t.ks = int(u % splits);
+    t.tidx = -1;
+  } else {
+    const uint32_t u = xcd_logical_id32(bid - whole, gridDim.x - whole);
+    t.tidx = int(u / tsp);
+    t.ks = int(u % tsp);
+    id = whole + u / tsp;
+  }
+  pp_place(id, tn, tm0, tm1, t);
+  return t;
+}
+
 // Ping-pong form of the 256 x 256 x 64 kernel.  The 8 waves form two groups
 // of four (one wave of each group per SIMD); group g owns output rows
-// [128 g, 128 g + 128) and each of its waves a 128 x 64 block.  The groups
-// alternate between a compute phase (the 32 MFMAs of one k-tile, fragments
-// read from LDS) and a memory phase (stage half of a later k-tile into LDS
-// and issue the global loads of the half after it), one workgroup barrier
-// per phase, offset by one phase: while one group's waves issue MFMAs the
-// other group's waves on the same SIMDs do the memory work, so the matrix
-// pipe of each SIMD is fed from one wave or the other in every phase.
-//   phase 2t:     group 0 computes k-tile t;  group 1 stages its half of
-//                 tile t + 1 and loads its half of tile t + 2;
-//   phase 2t + 1: group 1 computes k-tile t;  group 0 stages / loads the same.
-// Tile t lives in LDS buffer t mod 2: it is read in phases 2t and 2t + 1 and
-// written in phases 2t - 2 and 2t - 1, after tile t - 2 left that buffer.
-__global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmArgs a, float* __restrict__ partial,
-                                                          int splits, int64_t tail, int tsp) {
+// [128 g, 128 g + 128) and each of its waves a 128 x 64 block.  A group
+// alternates a memory phase (read the fragments of a whole k-tile from LDS
+// into registers, issue loads) with a compute phase (that k-tile's 32 MFMAs
+// and nothing else), one workgroup barrier per phase, the groups one phase
+// apart: each SIMD's matrix pipe is fed by one wave while the other does the
+// memory work.
+//   phase 2t:     group 0 reads k-tile t;      group 1 multiplies t - 1;
+//   phase 2t + 1: group 0 multiplies k-tile t;  group 1 reads t.
+// Tiles go from memory to LDS directly (buffer loads with the LDS flag), so
+// no registers stage them and the fragments of a whole tile fit.  All 160 KB
+// hold two A tiles and three W tiles.  Group 0 loads the second half of A
+// (rows 128..255, which only group 1 reads) of tile t + 1 and the first half
+// of W of tile t + 2 in phase 2t; group 1 the first half of A (read by group 0
+// only, so free after phase 2t) and the second half of W of tile t + 2 in
+// phase 2t + 1: every load is issued in a memory phase, each memory phase
+// issues the same eight per wave, and each load has at least two phases
+// (about 2000 cycles) before a barrier that waits for it.
+// Bound by: the clock under full matrix load.  The MFMAs alone (nothing loaded
+// or read) take 1.15 us per k-tile on 252 CUs and 0.9 on 144, this loop 1.42
+// and 0.92.  Measured (bias epilogue, TFLOP/s, before -> now; before: tiles
+// staged through registers and fragments read between the MFMAs): 1741 x 9216
+// x 3072 1023 -> 1250, 16896 x 12288 x 3072 1020 -> 1350, 8192^3 1090 -> 1458
+// (the vendor library: 1150, 1352, 1409).  Two tiles of each operand with all
+// loads in one phase ran 5 % slower at M = 1741 (the load unit needs 16
+// cycles per 1 KB load, a whole phase for a tile, and group 1's MFMAs queued
+// behind its loads); half k-tiles per phase (twice the barriers) 8 % slower;
+// without the raised priority in the compute phase 4-8 % slower.
+__global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmArgs args, float* __restrict__ partial,
+                                                          int splits, int tail, int tsp) {
   constexpr int BN = 256, WM = 128, WN = 64;
   constexpr int TM = WM / 32, TN = WN / 32;
-  constexpr int HALF = 4;                    // 16-byte chunks per thread per half-tile operand
-  __shared__ u32x4 lds[2][(kBM + BN) * 8];
+  constexpr int kOp = kBM * 8;               // 16-byte chunks of one operand's k-tile
+  // Two A buffers, then three W buffers (32 KB each): all 160 KB of the CU.
+  __shared__ u32x4 lds[5 * kOp];
 
-  int prob, ks;
-  int64_t m0, n0, tidx = -1;
-  if (tail > 0 ? !map_tile_tail(a, kBM, BN, tail, tsp, prob, m0, n0, ks, tidx)
-               : !map_tile(a, kBM, BN, splits, prob, m0, n0, ks))
-    return;
-  const GemmProblem p = prob ? a.p[1] : a.p[0];  // by value: a select, no indexed copy of the arguments
-  const bf16_t* A = static_cast<const bf16_t*>(p.A);
-  const bf16_t* W = static_cast<const bf16_t*>(p.W);
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+  // The arguments through the kernel-argument segment: a problem picked by a
+  // uniform index stays scalar loads (a copy would live in private memory).
+  const GemmArgsPtr a = (GemmArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  const int tn = int((a->N + BN - 1) / BN);
+  const int tm0 = int((a->p[0].M + kBM - 1) / kBM), tm1 = a->nprob > 1 ? int((a->p[1].M + kBM - 1) / kBM) : 0;
+  const PpTile tile = pp_tile(tn, tm0, tm1, splits, tail, tsp);
+  const int prob = tile.prob, ks = tile.ks, tidx = tile.tidx;
+  const GemmProblemPtr p = &a->p[prob];
+  const int64_t m0 = int64_t(tile.tm) * kBM, n0 = int64_t(tile.tn) * BN;
+  const int64_t M = p->M, N = a->N, K = a->K, lda = p->lda;
+  const bf16_t* A = static_cast<const bf16_t*>(p->A);
+  const bf16_t* W = static_cast<const bf16_t*>(p->W);
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int l32 = lane % 32, hi = lane / 32;
-  const int grp = __builtin_amdgcn_readfirstlane(wave / 4);
+  const int grp = wave / 4;
   const int wm = grp, wn = wave % 4;
 
   const int nsp = tidx >= 0 ? tsp : splits;
-  const int64_t nk = a.K / kBK;
-  const int64_t kt0 = nk * ks / nsp, kt1 = nk * (ks + 1) / nsp;
-  const int64_t n_t = kt1 - kt0;
+  const int nk = int(K / kBK);
+  const int kt0 = nk * ks / nsp, kt1 = nk * (ks + 1) / nsp;
+  const int n_t = kt1 - kt0;
 
-  // Staging of this group's half: A rows and W rows [128 grp, 128 grp + 128),
-  // thread tg moves chunk tg % 8 of rows tg / 8 + 32 j (one swizzle for all j).
-  const int tg = tid % 256;
-  const int row_t = tg / 8, kc_t = tg % 8;
-  const int slot_t = (128 * grp + row_t) * 8 + (kc_t ^ ((row_t >> 1) & 7));
-  uint32_t a_off[HALF], w_off[HALF];
+  // Staging: one load instruction moves 8 rows of 128 bytes; the LDS side is
+  // lane-linear, so the swizzle is applied to the chunk each lane fetches.
+  // Wave wn of a group moves rows 8 wn + 32 j (j = 0..3) of a 128-row half
+  // (one swizzle for all j): group 0 the second half of A and the first half
+  // of W, group 1 the first half of A and the second half of W.
+  const int row_t = wn * 8 + lane / 8;
+  const int kc_t = (lane % 8) ^ ((row_t >> 1) & 7);
+  const int a_half = 128 * (1 - grp), w_half = 128 * grp;
+  uint32_t a_off[4], w_off[4];
 #pragma unroll
-  for (int j = 0; j < HALF; ++j) {
-    a_off[j] = uint32_t(((128 * grp + row_t + 32 * j) * p.lda + kc_t * 8) * 2);
-    w_off[j] = uint32_t(((128 * grp + row_t + 32 * j) * a.K + kc_t * 8) * 2);
+  for (int j = 0; j < 4; ++j) {
+    a_off[j] = uint32_t(((a_half + row_t + 32 * j) * lda + kc_t * 8) * 2);
+    w_off[j] = uint32_t(((w_half + row_t + 32 * j) * K + kc_t * 8) * 2);
   }
-  const char* a_base = reinterpret_cast<const char*>(A + m0 * p.lda);
-  const char* w_base = reinterpret_cast<const char*>(W + n0 * a.K);
-  const int64_t a_bytes = (p.M - m0) * p.lda * 2, w_bytes = (a.N - n0) * a.K * 2;
-  // The staged loads stay in flight across the group's next compute phase
-  // (a loop-carried value), so they are compiler-visible buffer loads: the
-  // compiler places the vmcnt wait before the LDS store that consumes them.
-  u32x4 sa[HALF], sw[HALF];
-  auto load_half = [&](int64_t kt) {
-    const int64_t koff = kt * kBK * 2;
-    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<char*>(a_base + koff), 0, int(range32(a_bytes - koff)), 0x00020000);
-    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<char*>(w_base + koff), 0, int(range32(w_bytes - koff)), 0x00020000);
+  auto uniform = [](u32x4 r) {
 #pragma unroll
-    for (int j = 0; j < HALF; ++j) sa[j] = __builtin_amdgcn_raw_buffer_load_b128(ra, int(a_off[j]), 0, 0);
-#pragma unroll
-    for (int j = 0; j < HALF; ++j) sw[j] = __builtin_amdgcn_raw_buffer_load_b128(rw, int(w_off[j]), 0, 0);
+    for (int e = 0; e < 4; ++e) r[e] = __builtin_amdgcn_readfirstlane(r[e]);
+    return r;
   };
-  auto store_half = [&](int buf) {
+  const u32x4 ra = uniform(buffer_rsrc(A + m0 * lda, range32((M - m0) * lda * 2)));
+  const u32x4 rw = uniform(buffer_rsrc(W + n0 * K, range32((N - n0) * K * 2)));
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(uint32_t(reinterpret_cast<uintptr_t>(
+      (__attribute__((address_space(3))) char*)(&lds[0]))));
+  const uint32_t a_dst = lds0 + a_half * 128 + wn * 1024;
+  const uint32_t w_dst = lds0 + 2 * kOp * 16 + w_half * 128 + wn * 1024;
+  // This wave's share of k-tile t of A (buffer t mod 2) or W (slot ws).  Past
+  // the last k-tile the resource's range is 0: no memory is read, and the
+  // loads still count, so every wait below is the same constant.
+  auto load_a = [&](int t) {
+    const uint32_t koff = uint32_t(kt0 + t) * (kBK * 2);
+    const u32x4 r = {ra[0], ra[1], t < n_t ? ra[2] : 0u, ra[3]};
 #pragma unroll
-    for (int j = 0; j < HALF; ++j) lds[buf][slot_t + 256 * j] = sa[j];
+    for (int j = 0; j < 4; ++j) lds_load16(a_dst + (t & 1) * (kOp * 16), a_off[j], r, koff, 4096 * j);
+  };
+  auto load_w = [&](int t, int ws) {
+    const uint32_t koff = uint32_t(kt0 + t) * (kBK * 2);
+    const u32x4 r = {rw[0], rw[1], t < n_t ? rw[2] : 0u, rw[3]};
 #pragma unroll
-    for (int j = 0; j < HALF; ++j) lds[buf][kBM * 8 + slot_t + 256 * j] = sw[j];
+    for (int j = 0; j < 4; ++j) lds_load16(w_dst + ws * (kOp * 16), w_off[j], r, koff, 4096 * j);
   };
 
   f32x16 acc[TM][TN];
@@ -722,86 +974,95 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmArgs a, flo
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  auto compute = [&](int buf) {
-    const u32x4* L = lds[buf];
-    bf16x8 af[2][TM], wf[2][TN];
-    // Fragments are read in the order the next k step's MFMAs (i-major)
-    // consume them, so the first MFMAs wait on the oldest reads.
-    auto read = [&](int kk, int slot) {
-      const int chunk = 2 * kk + hi;
-      wf[slot][0] = as_bf16x8(L[kBM * 8 + swz(wn * WN + l32, chunk)]);
-      af[slot][0] = as_bf16x8(L[swz(wm * WM + l32, chunk)]);
+  // The fragments of a whole k-tile: read in one phase, multiplied in the next.
+  constexpr int KS = kBK / 16;
+  bf16x8 af[KS][TM], wf[KS][TN];
+  const int sw = (l32 >> 1) & 7;
+  const u32x4* La = lds + (wm * WM + l32) * 8;
+  const u32x4* Lw = lds + 2 * kOp + (wn * WN + l32) * 8;
+  auto read = [&](int t, int ws) {
 #pragma unroll
-      for (int j = 1; j < TN; ++j) wf[slot][j] = as_bf16x8(L[kBM * 8 + swz(wn * WN + 32 * j + l32, chunk)]);
+    for (int k = 0; k < KS; ++k) {
+      const int c = (2 * k + hi) ^ sw;
 #pragma unroll
-      for (int i = 1; i < TM; ++i) af[slot][i] = as_bf16x8(L[swz(wm * WM + 32 * i + l32, chunk)]);
-    };
-    read(0, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, TM + TN, 0);
+      for (int j = 0; j < TN; ++j) wf[k][j] = as_bf16x8(Lw[ws * kOp + 256 * j + c]);
 #pragma unroll
-    for (int kk = 0; kk < kBK / 16; ++kk) {
-      if (kk + 1 < kBK / 16) read(kk + 1, (kk + 1) & 1);
+      for (int i = 0; i < TM; ++i) af[k][i] = as_bf16x8(La[(t & 1) * kOp + 256 * i + c]);
+    }
+  };
+  auto mul = [&]() {
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int k = 0; k < KS; ++k)
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = mfma32x32x16(wf[kk & 1][j], af[kk & 1][i], acc[i][j]);
-      if (kk + 1 < kBK / 16) {
-#pragma unroll
-        for (int r = 0; r < TM + TN; ++r) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - (TM + TN), 0);
-      } else {
-        __builtin_amdgcn_sched_group_barrier(0x008, TM * TN, 0);
-      }
-    }
+        for (int j = 0; j < TN; ++j) acc[i][j] = mfma32x32x16(wf[k][j], af[k][i], acc[i][j]);
+    __builtin_amdgcn_s_setprio(0);
+  };
+  auto bar = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    lds_barrier();
+    __builtin_amdgcn_sched_barrier(0);
   };
 
-  if (n_t > 0) {
-    load_half(kt0);
-    store_half(0);
-    if (n_t > 1) load_half(kt0 + 1);
-  }
-  lds_barrier();
-  // Memory phase of k-tile t: stage this group's half of tile t + 1, then
-  // issue its loads of tile t + 2.
-  auto memory = [&](int64_t t) {
-    if (t + 1 < n_t) {
-      store_half(int((t + 1) & 1));
-      if (t + 2 < n_t) load_half(kt0 + t + 2);
-    }
-  };
   // Each group runs its own straight loop; both pass the same barriers.
+  load_a(0);
+  load_w(0, 0);
+  int ws = 0, ws2 = 2;   // W slots of tiles t and t + 2
+  auto next_slot = [&]() {
+    ws2 = ws;
+    ws = ws == 2 ? 0 : ws + 1;
+  };
   if (grp == 0) {
-    for (int64_t t = 0; t < n_t; ++t) {
-      compute(int(t & 1));
-      lds_barrier();
-      memory(t);
-      lds_barrier();
+    load_w(1, 1);
+    vm_wait<4>();
+    bar();
+    for (int t = 0; t < n_t; ++t) {
+      read(t, ws);
+      load_a(t + 1);
+      load_w(t + 2, ws2);
+      vm_wait<12>();   // phase 2t + 1 reads the A half loaded in phase 2t - 2
+      bar();
+      mul();
+      vm_wait<8>();    // phase 2t + 2 reads the W half loaded in phase 2t - 2
+      bar();
+      next_slot();
     }
+    vm_wait<0>();
+    bar();
   } else {
-    for (int64_t t = 0; t < n_t; ++t) {
-      memory(t);
-      lds_barrier();
-      compute(int(t & 1));
-      lds_barrier();
+    load_a(1);
+    load_w(1, 1);
+    vm_wait<8>();
+    bar();
+    if (n_t == 0) vm_wait<0>();
+    bar();
+    for (int t = 0; t < n_t; ++t) {
+      read(t, ws);
+      load_a(t + 2);
+      load_w(t + 2, ws2);
+      vm_wait<8>();    // phase 2t + 2 reads what phase 2t - 1 loaded
+      bar();
+      mul();
+      if (t == n_t - 1) vm_wait<0>();
+      bar();
+      next_slot();
     }
   }
 
   // Split partials: a tail tile's go to its own 256 x 256 block (split-major),
   // a fully split launch's to rows of the [split][row][N] array.
   float* pbase = nullptr;
-  int64_t pld = a.N;
+  int64_t pld = N;
   if (tidx >= 0) {
-    pbase = partial + (tidx * tsp + ks) * int64_t(kBM * BN);
+    pbase = partial + (int64_t(tidx) * tsp + ks) * (kBM * BN);
     pld = BN;
   } else if (splits > 1) {
-    const int64_t rows_all = a.p[0].M + (a.nprob > 1 ? a.p[1].M : 0);
-    pbase = partial + (int64_t(ks) * rows_all + (prob ? a.p[0].M : 0) + m0) * a.N + n0;
+    const int64_t M0 = a->p[0].M, rows_all = M0 + (a->nprob > 1 ? a->p[1].M : 0);
+    pbase = partial + (ks * rows_all + (prob ? M0 : 0) + m0) * N + n0;
   }
-  staged_epilogue<WM, WN, TM, TN>(a, p, m0, n0, pbase != nullptr, pbase, pld, acc,
-                                  reinterpret_cast<float*>(&lds[0][0]), wave, wm, wn, lane);
+  pp_epilogue<TM, TN>(a, p, m0, n0, pbase, pld, acc, lds, wave, wm, wn, lane);
 }
 
 // Sum the k splits of each tail tile in split order and apply the epilogue.
@@ -813,11 +1074,12 @@ __global__ __launch_bounds__(256) void tail_reduce_kernel(const GemmArgs a, cons
   const int64_t t = blockIdx.x / (kBM / 8);
   const int r = int(blockIdx.x % (kBM / 8)) * 8 + int(threadIdx.x) / 32;
   const int c = (int(threadIdx.x) % 32) * 8;
-  int prob;
-  int64_t m0, n0;
-  if (!decode_tile(a, kBM, BN, tiles_total(a, kBM, BN) - tail + t, prob, m0, n0)) return;
-  const GemmProblem p = prob ? a.p[1] : a.p[0];
-  const int64_t m = m0 + r, n = n0 + c;
+  const uint32_t tn = uint32_t((a.N + BN - 1) / BN), tm0 = uint32_t((a.p[0].M + kBM - 1) / kBM);
+  const uint32_t tm1 = a.nprob > 1 ? uint32_t((a.p[1].M + kBM - 1) / kBM) : 0u;
+  PpTile pt;
+  pp_place(uint32_t(tn * (tm0 + tm1) - tail + t), tn, tm0, tm1, pt);
+  const GemmProblem p = pt.prob ? a.p[1] : a.p[0];
+  const int64_t m = int64_t(pt.tm) * kBM + r, n = int64_t(pt.tn) * BN + c;
   if (m >= p.M || n >= a.N) return;
   const float* src = partial + t * tsp * int64_t(kBM * BN) + r * BN + c;
   float v[8];
@@ -909,6 +1171,26 @@ int64_t tiles_of(const GemmArgs& a, int bm, int bn) {
   return t;
 }
 
+// What the ping-pong kernel's 16-byte accesses and 64-column strips assume:
+// the library's own buffers and 16-byte aligned tensors always meet it;
+// anything else (a bias that is a slice at an odd element, say) takes the
+// 128-wide kernel, whose accesses are narrower.  A transposed output may
+// start anywhere.
+bool pp_layout_ok(const GemmArgs& a) {
+  auto off = [](const void* ptr) { return reinterpret_cast<uintptr_t>(ptr) % 16; };
+  if (a.N % 8 != 0 || (a.n_split < a.N && a.n_split % 64 != 0) || (a.n_split2 < a.N && a.n_split2 % 64 != 0))
+    return false;
+  for (int i = 0; i < a.nprob; ++i) {
+    const GemmProblem& p = a.p[i];
+    if (off(p.A) || off(p.W) || off(p.bias) || off(p.gate) || off(p.resid) || off(p.scat)) return false;
+    if (p.lda % 8 || p.ldr % 8 || p.scat_ld % 8) return false;
+    if (a.mode0 != EPI_STORE_T && (off(p.out0) || p.ld0 % 8)) return false;
+    if (a.n_split < a.N && a.mode1 != EPI_STORE_T && (off(p.out1) || p.ld1 % 8)) return false;
+    if (a.n_split2 < a.N && a.mode2 != EPI_STORE_T && (off(p.out2) || p.ld2 % 8)) return false;
+  }
+  return true;
+}
+
 }  // namespace
 
 GemmPlan plan_gemm(const GemmArgs& a, int dtype, size_t partial_bytes, const char* family) {
@@ -925,12 +1207,13 @@ GemmPlan plan_gemm(const GemmArgs& a, int dtype, size_t partial_bytes, const cha
   // extra fp32 partial traffic of a split.
   const int cands[3] = {256, 192, 128};
   const double eff[3] = {1.0, 0.74, 0.65};
+  const bool wide = pp_layout_ok(a);
   const int64_t nk = a.K / kBK;
   const int64_t rows = a.p[0].M + (a.nprob > 1 ? a.p[1].M : 0);
   double best = -1.0;
   for (int c = 0; c < 3; ++c) {
     const int64_t t = tiles_of(a, kBM, cands[c]);
-    if (t == 0) continue;
+    if (t == 0 || (cands[c] == 256 && !wide)) continue;
     for (int sp = 1; sp <= 4; ++sp) {
       if (sp > 1 && (nk / sp < 4 || size_t(sp) * size_t(rows) * size_t(a.N) * sizeof(float) > partial_bytes)) break;
       const int64_t units = t * sp;
@@ -983,6 +1266,7 @@ GemmPlan plan_gemm(const GemmArgs& a, int dtype, size_t partial_bytes, const cha
   if (env) {
     int bn = 0, sp = 0, wv = 8, stg = 2, tail = 0, tsp = 1;
     const int got = sscanf(env, "%d,%d,%d,%d,%d,%d", &bn, &sp, &wv, &stg, &tail, &tsp);
+    if (bn == 256 && !wide) bn = 128;
     if (got >= 2 && (bn == 256 || bn == 192 || bn == 128) && sp >= 1 && sp <= 4 && wv == 8 &&
         (stg == 1 || stg == 2)) {
       pl.bn = bn;
@@ -1036,7 +1320,7 @@ int launch_gemm(const GemmArgs& a, int dtype, hipStream_t s, const char* family,
     TimedLaunch timed(family, s);  // the GEMM kernel alone; the reduce is its own family
     switch (pl.bn * 100 + pl.waves * 10 + pl.stages) {
       case 25681:
-        hipLaunchKernelGGL(gemm_bf16_pp_kernel, grid, dim3(512), 0, s, a, partial, pl.splits, pl.tail,
+        hipLaunchKernelGGL(gemm_bf16_pp_kernel, grid, dim3(512), 0, s, a, partial, pl.splits, int(pl.tail),
                            pl.tail_splits);
         break;
       case 19281: hipLaunchKernelGGL((gemm_bf16_kernel<192, 4, 2, 1>), grid, dim3(512), 0, s, a, partial, pl.splits); break;
