@@ -44,6 +44,7 @@ struct AttnUnit {
   int h;
   int64_t q_lo, q_hi;
   int64_t ks[2], kn[2];
+  int lead[2];  // keys at the start of each range that belong to another sequence
 };
 
 // Number of row blocks of `rows` query rows per head.
@@ -129,6 +130,14 @@ __device__ __forceinline__ AttnUnit attn_unit(const AttnArgs& a, int rows, int64
     piece = v;
   }
   AttnUnit w = attn_decode(a, rows, u);
+  // Tiles start on 8-key boundaries, so that the 16-byte V^T loads are
+  // aligned; the keys before the range are masked.
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    w.lead[r] = w.kn[r] > 0 ? int(w.ks[r] & 7) : 0;
+    w.ks[r] -= w.lead[r];
+    w.kn[r] += w.lead[r];
+  }
   if (piece >= 0) {
     const int64_t t0 = (w.kn[0] + 63) / 64, T = t0 + (w.kn[1] + 63) / 64;
     const int64_t t_lo = T * p / a.ksp, t_hi = T * (p + 1) / a.ksp;
@@ -141,6 +150,8 @@ __device__ __forceinline__ AttnUnit attn_unit(const AttnArgs& a, int rows, int64
     w.kn[0] = n0;
     w.ks[1] += 64 * a1;
     w.kn[1] = n1;
+    if (a0 > 0) w.lead[0] = 0;
+    if (a1 > 0) w.lead[1] = 0;
   }
   return w;
 }
@@ -152,28 +163,27 @@ __device__ __forceinline__ AttnUnit attn_unit(const AttnArgs& a, int rows, int64
 // holds key 16*(r/8) + 8h + 4*((r/4)%2) + r%4 of its 32-key sub-tile: for
 // the 16-key chunk c of the P^T operand, lane half h then holds the
 // contiguous keys 16c + 8h .. +7, and each V^T operand is a single 16-byte
-// LDS read (V^T rows padded to a 16-byte multiple).  The last, partial key
-// tile runs through its own instance of the tile body (key masking, V^T
-// zeroing), so full tiles carry no tail arithmetic; the text-mass sum is
-// compiled in only when MASS is set.
+// LDS read.
 template <int DH, bool WITH_V, bool MASS>
 __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const AttnArgs a) {
   constexpr int NW = kRows / 32;             // waves
   constexpr int kKT = 64;                    // keys per tile
-  constexpr int kT = 64 * NW;                // threads
-  constexpr int kC = DH / 16;
-  constexpr int kKL = DH + 8;                // padded K row (elements), 16-byte multiple
-  constexpr int kVL = kKT + 8;               // padded V^T row (elements), 16-byte multiple
-  constexpr int kKP = kKT * DH / 8 / kT;     // 16-byte K pieces per thread per tile
-  constexpr int kVP = DH * kKT / 8 / kT;     // 16-byte V^T pieces per thread per tile
-  static_assert(kKP >= 1 && kVP >= 1, "tile too small for the workgroup");
-  __shared__ __attribute__((aligned(16))) bf16_t Ks[2][kKT * kKL];
-  __shared__ __attribute__((aligned(16))) bf16_t Vs[2][WITH_V ? DH * kVL : 8];
+  constexpr int kC = DH / 16;                // k steps of S
+  constexpr int kDT = WITH_V ? DH / 32 : 1;  // 32-row tiles of O^T
+  constexpr int kKC = DH / 8;                // 16-byte chunks per K row
+  constexpr int kKR = kWave / kKC;           // K rows per load instruction
+  constexpr int kKB = kKT * DH * 2, kVB = DH * kKT * 2;  // bytes of a K and a V^T tile
+  constexpr int kKL = kKB / 1024 / NW, kVL = kVB / 1024 / NW;  // load instructions per wave and tile
+  // Two K tiles, then two V^T tiles, without padding: 16-byte chunk c of K row
+  // r is at c ^ (r mod 16) (128-byte rows, DH = 64: c ^ (r / 2 mod 8)), of
+  // V^T row r at c ^ (r / 2 mod 8): the fragment reads are conflict-free.
+  __shared__ __attribute__((aligned(16))) char smem[2 * kKB + (WITH_V ? 2 * kVB : 0)];
 
   int64_t piece;
   const AttnUnit un = attn_unit(a, 32 * NW, piece);
   const int h = un.h;
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int l32 = lane % 32, hi = lane / 32;
   const int64_t row = un.q_lo + wave * 32 + l32;
   const bf16_t* Q = static_cast<const bf16_t*>(a.q);
@@ -188,207 +198,304 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const AttnArgs a) {
   }
   const float scale2 = kLog2e * rsqrtf(float(DH));
   float mrow = -INFINITY, lrow = 0.f, trow = 0.f;
-  f32x16 oacc[WITH_V ? DH / 32 : 1];
+  f32x16 oacc[kDT];
 #pragma unroll
-  for (int dt = 0; dt < (WITH_V ? DH / 32 : 1); ++dt)
+  for (int dt = 0; dt < kDT; ++dt)
 #pragma unroll
     for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
 
-  // Per-thread piece coordinates (fixed over the tiles).
-  int k_key[kKP], k_dst[kKP], v_dv[kVP], v_kc[kVP];
-  const bf16_t* k_src[kKP];
-  const bf16_t* v_src[kVP];
+  // Staging: a load instruction moves 1 KB straight to LDS (lane-linear, so
+  // the swizzle and the key permutation are applied to each lane's source).
+  auto swz_k = [](int r) { return DH == 128 ? r & 15 : (r >> 1) & 7; };
+  uint32_t k_off[kKL], v_off[kVL];
 #pragma unroll
-  for (int j = 0; j < kKP; ++j) {
-    const int p = tid + kT * j;
-    const int kk = p / (DH / 8), col = (p % (DH / 8)) * 8;
-    k_key[j] = kk;
-    const int rowp = (kk & ~12) | ((kk & 4) << 1) | ((kk & 8) >> 1);
-    k_dst[j] = rowp * kKL + col;
-    k_src[j] = K + int64_t(kk) * a.k_tok + col;
+  for (int j = 0; j < kKL; ++j) {
+    const int r = kKR * (wave + NW * j) + lane / kKC;
+    const int key = (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1);
+    k_off[j] = uint32_t(key) * uint32_t(a.k_tok * 2) + uint32_t(((lane % kKC) ^ swz_k(r)) * 16);
   }
 #pragma unroll
-  for (int j = 0; j < kVP; ++j) {
-    const int p = tid + kT * j;
-    v_dv[j] = p / (kKT / 8);
-    v_kc[j] = (p % (kKT / 8)) * 8;
-    v_src[j] = VT + int64_t(v_dv[j]) * a.ldvt + v_kc[j];
+  for (int j = 0; j < kVL; ++j) {
+    const int r = 8 * (wave + NW * j) + lane / 8;
+    v_off[j] = uint32_t(r) * uint32_t(a.ldvt * 2) + uint32_t(((lane % 8) ^ ((r >> 1) & 7)) * 16);
   }
-  // Register prefetch of the next tile.
-  u32x4 kreg[kKP], vreg[WITH_V ? kVP : 1];
-  // Tile of key rows k0 .. k0 + rem - 1 (rem < kKT: the partial tile at the
-  // end of a key range).
-  auto load_tile = [&](int64_t k0, int rem) {
-    if (rem == kKT) {
-#pragma unroll
-      for (int j = 0; j < kKP; ++j) kreg[j] = *reinterpret_cast<const u32x4*>(k_src[j] + k0 * a.k_tok);
-      if constexpr (WITH_V) {
-#pragma unroll
-        for (int j = 0; j < kVP; ++j) vreg[j] = *reinterpret_cast<const u32x4*>(v_src[j] + k0);
-      }
-    } else {
-      // Clamp key rows; zero V^T beyond the end so that 0-probability keys
-      // contribute exactly 0.
-#pragma unroll
-      for (int j = 0; j < kKP; ++j) {
-        const int kk = std::min(k_key[j], rem - 1);
-        kreg[j] = *reinterpret_cast<const u32x4*>(k_src[j] + (k0 + kk - k_key[j]) * a.k_tok);
-      }
-      if constexpr (WITH_V) {
-#pragma unroll
-        for (int j = 0; j < kVP; ++j) {
-          vreg[j] = *reinterpret_cast<const u32x4*>(v_src[j] + k0);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int kk = v_kc[j] + 2 * e;
-            vreg[j][e] = (kk < rem ? vreg[j][e] & 0xffffu : 0u) | (kk + 1 < rem ? vreg[j][e] & 0xffff0000u : 0u);
-          }
-        }
-      }
-    }
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(uint32_t(reinterpret_cast<uintptr_t>(
+      (__attribute__((address_space(3))) char*)(&smem[0]))));
+  const uint32_t lds_w = lds0 + wave * 1024;
+  const int64_t k_bytes = ((a.Sk - 1) * a.k_tok + DH) * 2, v_bytes = int64_t(DH) * a.ldvt * 2;
+
+  // Key tiles: those of the first key range, then the second's.
+  const int t0 = int((un.kn[0] + kKT - 1) / kKT);
+  const int n_tiles = t0 + int((un.kn[1] + kKT - 1) / kKT);
+  // First key of tile `it` and the keys [lo, up) of it that count.
+  auto tile_at = [&](int it, int64_t& base, int& lo, int& up) {
+    const bool first = it < t0;  // selects, not a dynamic index into un.ks / un.kn
+    const int local = first ? it : it - t0;
+    base = (first ? un.ks[0] : un.ks[1]) + int64_t(local) * kKT;
+    lo = local == 0 ? (first ? un.lead[0] : un.lead[1]) : 0;
+    up = int(std::min<int64_t>(kKT, (first ? un.kn[0] : un.kn[1]) - int64_t(local) * kKT));
   };
-  auto store_tile = [&](int buf) {
+  // Loads past the last tile have an empty range (nothing is read); rows or
+  // columns past the end of K or V^T come back as zeros.
+  auto uniform = [](u32x4 r) {
 #pragma unroll
-    for (int j = 0; j < kKP; ++j) *reinterpret_cast<u32x4*>(&Ks[buf][k_dst[j]]) = kreg[j];
+    for (int e = 0; e < 4; ++e) r[e] = __builtin_amdgcn_readfirstlane(r[e]);
+    return r;
+  };
+  auto load_k = [&](int it) {
+    int64_t base;
+    int lo, up;
+    tile_at(it, base, lo, up);
+    if (it >= n_tiles) return;
+    const u32x4 r = uniform(buffer_rsrc(K + base * a.k_tok, range32(k_bytes - base * a.k_tok * 2)));
+    const uint32_t dst = lds_w + (it & 1) * kKB;
+#pragma unroll
+    for (int j = 0; j < kKL; ++j) lds_load16(dst, k_off[j], r, 0, 1024 * NW * j);
+  };
+  auto load_v = [&](int it) {
     if constexpr (WITH_V) {
+      int64_t base;
+      int lo, up;
+      tile_at(it, base, lo, up);
+      const u32x4 r = uniform(buffer_rsrc(VT + base, range32(v_bytes - base * 2)));
+      const uint32_t dst = lds_w + 2 * kKB + (it & 1) * kVB;
 #pragma unroll
-      for (int j = 0; j < kVP; ++j) *reinterpret_cast<u32x4*>(&Vs[buf][v_dv[j] * kVL + v_kc[j]]) = vreg[j];
+      for (int j = 0; j < kVL; ++j) lds_load16(dst, v_off[j], r, 0, 1024 * NW * j);
     }
   };
   // Key (within the tile) of accumulator register r of sub-tile t, less 8 h.
   auto key_of = [](int t, int r) { return 32 * t + 16 * (r / 8) + 4 * ((r / 4) & 1) + (r % 4); };
 
-  // Key tiles: ceil(kn[0] / kKT) over the first range, then the second's.
-  const int64_t t0 = (un.kn[0] + kKT - 1) / kKT;
-  const int64_t n_tiles = t0 + (un.kn[1] + kKT - 1) / kKT;
-  auto tile_at = [&](int64_t it, int64_t& base, int& rem) {
-    const bool first = it < t0;  // selects, not a dynamic index into un.ks / un.kn
-    const int64_t local = (first ? it : it - t0) * kKT;
-    base = (first ? un.ks[0] : un.ks[1]) + local;
-    rem = int(std::min<int64_t>(kKT, (first ? un.kn[0] : un.kn[1]) - local));
+  const int sk = hi ^ swz_k(l32), sv = hi ^ ((l32 >> 1) & 7);
+  typedef f32x16 STile[kKT / 32];
+  typedef bf16x8 PTile[kKT / 16];
+  constexpr int kQK = kC * (kKT / 32), kPV = WITH_V ? kDT * (kKT / 16) : 0;
+  constexpr int kRd = 4;  // fragments read ahead of their product
+  // Products 0 .. kQK - 1 of a step are those of S = K Q^T (two independent
+  // chains), the next kPV those of O^T += V^T P^T (kDT chains).
+  auto fragment = [&](int i, int kbuf, int vbuf) {
+    if (i < kQK) {
+      const int c = i / 2, t = i % 2;
+      return as_bf16x8(*reinterpret_cast<const u32x4*>(smem + kbuf * kKB + (l32 + 32 * t) * (DH * 2) +
+                                                       ((2 * c) ^ sk) * 16));
+    }
+    const int c = (i - kQK) / kDT, dt = (i - kQK) % kDT;
+    return as_bf16x8(*reinterpret_cast<const u32x4*>(smem + 2 * kKB + vbuf * kVB + (l32 + 32 * dt) * (kKT * 2) +
+                                                     ((2 * c) ^ sv) * 16));
   };
-  int buf = 0;
-  // Key tile `it` (rows k0 .. k0 + rem - 1; its key index within a range
-  // starting at 0 is k0 - ks[0] for the text-mass test): prefetch tile it + 1
-  // into registers, consume tile it from LDS, stage tile it + 1 in the other
-  // LDS buffer.
-  auto tile = [&](int64_t it, int64_t k0, int rem, auto tail_tag) {
-    constexpr bool kTail = decltype(tail_tag)::value;
-    const bool more = it + 1 < n_tiles;
-    if (more) {
-      int64_t nb;
-      int nr;
-      tile_at(it + 1, nb, nr);
-      load_tile(nb, nr);
+  auto product = [&](int i, const bf16x8& f, STile& sn, const PTile& pp) {
+    if (i < kQK) {
+      const int c = i / 2, t = i % 2;
+      sn[t] = mfma32(f, qf[c], c == 0 ? f32x16{} : sn[t]);
+    } else {
+      const int c = (i - kQK) / kDT, dt = (i - kQK) % kDT;
+      oacc[dt] = mfma32(f, pp[c], oacc[dt]);
     }
-
-    f32x16 s[kKT / 32];
-#pragma unroll
-    for (int t = 0; t < kKT / 32; ++t) {
-      f32x16 acc;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll
-      for (int c = 0; c < kC; ++c) {
-        const bf16x8 kf = as_bf16x8(*reinterpret_cast<const u32x4*>(&Ks[buf][(32 * t + l32) * kKL + 16 * c + 8 * hi]));
-        acc = mfma32(kf, qf[c], acc);
-      }
-      s[t] = acc;
-    }
-    if constexpr (kTail) {
-      const int lim = rem - 8 * hi;
-#pragma unroll
-      for (int t = 0; t < kKT / 32; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (key_of(t, r) >= lim) s[t][r] = -INFINITY;
-    }
-    float mx = -INFINITY;
+  };
+  // Keys of tile `it` that do not count: logits to -inf.
+  auto mask = [&](int it, STile& s) {
+    int64_t k0;
+    int lo, up;
+    tile_at(it, k0, lo, up);
+    if (lo == 0 && up == kKT) return;
+    asm volatile("" ::: "memory");  // rare: a branch, not 32 selects on every tile
+    const int l = lo - 8 * hi, u = up - 8 * hi;
 #pragma unroll
     for (int t = 0; t < kKT / 32; ++t)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[t][r]);
-    mx = max_xor32(mx) * scale2;
-    const bool raise = mx > mrow + 8.f;
-    float corr = 1.f;
-    if (raise) {
-      corr = __builtin_amdgcn_exp2f(mrow - mx);
-      mrow = mx;
-    }
-    float ls = 0.f;
+      for (int r = 0; r < 16; ++r)
+        if (key_of(t, r) < l || key_of(t, r) >= u) s[t][r] = -INFINITY;
+  };
+  // Logits of a tile to probabilities, without a branch, in slices
+  // 0 .. n - 1 (in order): the row maximum over the first slices, then the
+  // running maximum, then the exponentials and their sum.  corr is the factor
+  // the output so far must be multiplied by (1 unless the maximum rose).
+  float corr = 1.f, ls = 0.f, mx = -INFINITY;
+  auto softmax_slice = [&](int i, int n, STile& s, PTile& p) {
+    const int n_max = n / 5, e0 = n_max + 1;
+    if (i < n_max) {
+      if (i == 0) mx = -INFINITY;
 #pragma unroll
-    for (int t = 0; t < kKT / 32; ++t)
+      for (int e = 0; e < 32; ++e)
+        if (e >= 32 * i / n_max && e < 32 * (i + 1) / n_max) mx = fmaxf(mx, s[e / 16][e % 16]);
+    } else if (i == n_max) {
+      mx = max_xor32(mx) * scale2;
+      const float m_new = mx > mrow + 8.f ? mx : mrow;
+      corr = __builtin_amdgcn_exp2f(mrow - m_new);
+      mrow = m_new;
+      ls = 0.f;
+    } else {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float e = __builtin_amdgcn_exp2f(fmaf(s[t][r], scale2, -mrow));
-        s[t][r] = e;
-        ls += e;
-      }
-    lrow = lrow * corr + ls;
-    if constexpr (MASS) {
-      if (k0 < a.mass_keys) {
-        float ts = ls;
-        if (k0 + kKT > a.mass_keys) {
-          ts = 0.f;
-          const int lim = int(a.mass_keys - k0) - 8 * hi;
-#pragma unroll
-          for (int t = 0; t < kKT / 32; ++t)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) ts += key_of(t, r) < lim ? s[t][r] : 0.f;
+      for (int e = 0; e < 32; ++e) {
+        if (e < 32 * (i - e0) / (n - e0) || e >= 32 * (i + 1 - e0) / (n - e0)) continue;
+        const float v = __builtin_amdgcn_exp2f(fmaf(s[e / 16][e % 16], scale2, -mrow));
+        s[e / 16][e % 16] = v;
+        ls += v;
+        if constexpr (WITH_V) {
+          if (e % 2 == 1) {
+            u32x4 w = __builtin_bit_cast(u32x4, p[e / 8]);
+            w[(e % 8) / 2] = pack_bf2(s[e / 16][e % 16 - 1], v);
+            p[e / 8] = as_bf16x8(w);
+          }
         }
-        trow = trow * corr + ts;
-      } else {
-        trow *= corr;
       }
+      if (i == n - 1) lrow = lrow * corr + ls;
+    }
+  };
+  // The rest of a step, after its products: the text mass of tile `it` and
+  // the rescaled output.
+  auto finish = [&](int it, const STile& s) {
+    if constexpr (MASS) {
+      int64_t k0;
+      int lo, up;
+      tile_at(it, k0, lo, up);
+      float ts = k0 < a.mass_keys ? ls : 0.f;
+      if (k0 < a.mass_keys && k0 + kKT > a.mass_keys) {
+        asm volatile("" ::: "memory");
+        ts = 0.f;
+        const int lim = int(a.mass_keys - k0) - 8 * hi;
+#pragma unroll
+        for (int t = 0; t < kKT / 32; ++t)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) ts += key_of(t, r) < lim ? s[t][r] : 0.f;
+      }
+      trow = trow * corr + ts;
     }
     if constexpr (WITH_V) {
-      if (__any(raise)) {
+      if (__any(corr != 1.f)) {
         // Rare (the max rises by more than 8): keep it a branch, not a
         // multiply by 1 on every tile.
         asm volatile("" ::: "memory");
 #pragma unroll
-        for (int dt = 0; dt < DH / 32; ++dt) oacc[dt] *= corr;
-      }
-#pragma unroll
-      for (int c = 0; c < kKT / 16; ++c) {
-        const f32x16& st = s[c / 2];
-        const int b = 8 * (c % 2);
-        const u32x4 pv = {pack_bf2(st[b + 0], st[b + 1]), pack_bf2(st[b + 2], st[b + 3]),
-                          pack_bf2(st[b + 4], st[b + 5]), pack_bf2(st[b + 6], st[b + 7])};
-        const bf16x8 pf = as_bf16x8(pv);
-#pragma unroll
-        for (int dt = 0; dt < DH / 32; ++dt) {
-          const u32x4 vv = *reinterpret_cast<const u32x4*>(&Vs[buf][(32 * dt + l32) * kVL + 16 * c + 8 * hi]);
-          oacc[dt] = mfma32(as_bf16x8(vv), pf, oacc[dt]);
-        }
+        for (int dt = 0; dt < kDT; ++dt) oacc[dt] *= corr;
       }
     }
-    if (more) store_tile(buf ^ 1);
+  };
+  // Products [lo, up) of a step with the softmax of (s, p) spread over them
+  // (SOFTMAX), in this order: the compiler, left to itself, puts the products
+  // first and the softmax after them, which serialises the two units.
+  auto run = [&](auto lo_tag, auto up_tag, auto soft_tag, int kbuf, int vbuf, STile& s, STile& sn, const PTile& pp,
+                 PTile& p) {
+    constexpr int lo = decltype(lo_tag)::value, up = decltype(up_tag)::value;
+    constexpr bool soft = decltype(soft_tag)::value;
+    constexpr int n = up - lo > 10 ? up - lo : 10;  // slots
+    bf16x8 f[kRd];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = lo; i < up && i < lo + kRd; ++i) f[(i - lo) % kRd] = fragment(i, kbuf, vbuf);
+#pragma unroll
+    for (int i = lo; i < lo + n; ++i) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (i < up) {
+        product(i, f[(i - lo) % kRd], sn, pp);
+        if (i + kRd < up) f[(i - lo) % kRd] = fragment(i + kRd, kbuf, vbuf);
+      }
+      if (soft) softmax_slice(i - lo, n, s, p);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  using Yes = std::integral_constant<bool, true>;
+  using No = std::integral_constant<bool, false>;
+  using Zero = std::integral_constant<int, 0>;
+  using Qk = std::integral_constant<int, kQK>;
+  using All = std::integral_constant<int, kQK + kPV>;
+  // V^T columns of tile `it` that do not count become zeros (their
+  // probabilities are 0, but the memory behind them may hold anything).
+  auto clear_v = [&](int it) {
+    if constexpr (WITH_V) {
+      int64_t k0;
+      int lo, up;
+      tile_at(it, k0, lo, up);
+      if (lo == 0 && up == kKT) return;
+      for (int i = tid; i < DH * 8; i += 64 * NW) {
+        const int r = i / 8, c = i % 8;
+        u32x4* d = reinterpret_cast<u32x4*>(smem + 2 * kKB + (it & 1) * kVB + r * (kKT * 2) + (c ^ ((r >> 1) & 7)) * 16);
+        if (8 * c >= lo && 8 * c + 8 <= up) continue;
+        u32x4 v = *d;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int k = 8 * c + 2 * e;
+          v[e] = (k >= lo && k < up ? v[e] & 0xffffu : 0u) | (k + 1 >= lo && k + 1 < up ? v[e] & 0xffff0000u : 0u);
+        }
+        *d = v;
+      }
+      lds_barrier();
+    }
+  };
+  // The loads issued one step ago have landed, for every wave.
+  auto step_barrier = [&]() {
+    vm_wait<0>();
+    __builtin_amdgcn_sched_barrier(0);
     lds_barrier();
-    buf ^= 1;
+    __builtin_amdgcn_sched_barrier(0);
   };
 
-  {
-    int64_t b0;
-    int r0;
-    tile_at(0, b0, r0);
-    load_tile(b0, r0);
-  }
-  store_tile(0);
-  lds_barrier();
-  // Per key range: its full tiles, then its partial tile through the tail
-  // instance of the body (so the hot loop holds the full-tile body only).
-  int64_t it = 0;
+  // Step t: the products that do not depend on this tile's softmax, P(t - 1)
+  // V(t - 1) and S(t + 1), run on the matrix pipe while the softmax of S(t)
+  // runs on the vector units.  K(t + 2) and V(t) are loaded meanwhile (into the
+  // buffers of K(t) and V(t - 2), which the last step was the last to read).
+  STile sa, sb;
+  PTile pa, pb;
+  load_k(0);
+  step_barrier();
+  if (n_tiles > 1) load_k(1);
+  run(Zero(), Qk(), No(), 0, 0, sb, sa, pa, pa);
+  // The step's results are made in it, not sunk to where they are used.
+  auto pin = [&](STile& sn, PTile& p) {
 #pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const int64_t n_full = un.kn[r] / kKT;
-    const int rem_last = int(un.kn[r] % kKT);
-    for (int64_t f = 0; f < n_full; ++f, ++it) tile(it, un.ks[r] + f * kKT, kKT, std::integral_constant<bool, false>());
-    if (rem_last) {
-      tile(it, un.ks[r] + n_full * kKT, rem_last, std::integral_constant<bool, true>());
-      ++it;
+    for (int i = 0; i < kKT / 32; ++i) asm volatile("" : "+v"(sn[i]));
+    if constexpr (WITH_V) {
+#pragma unroll
+      for (int i = 0; i < kKT / 16; ++i) asm volatile("" : "+v"(p[i]));
+#pragma unroll
+      for (int i = 0; i < kDT; ++i) asm volatile("" : "+v"(oacc[i]));
     }
+    asm volatile("" : "+v"(lrow));
+  };
+  auto middle = [&](int t, int buf, STile& s, STile& sn, PTile& pp, PTile& p) {  // buf = (t - 1) & 1
+    step_barrier();
+    load_k(t + 2);
+    load_v(t);
+    clear_v(t - 1);
+    mask(t, s);
+    run(Zero(), All(), Yes(), buf, buf, s, sn, pp, p);
+    pin(sn, p);
+    finish(t, s);
+  };
+  step_barrier();
+  load_k(2);
+  load_v(0);
+  mask(0, sa);
+  if (n_tiles > 1) run(Zero(), Qk(), No(), 1, 0, sb, sb, pa, pa);
+  run(Zero(), Zero(), Yes(), 0, 0, sa, sb, pa, pa);
+  finish(0, sa);
+  if (n_tiles > 1) {
+    int t = 1;
+    for (; t + 2 < n_tiles; t += 2) {
+      middle(t, 0, sb, sa, pa, pb);
+      middle(t + 1, 1, sa, sb, pb, pa);
+    }
+    if (t + 1 < n_tiles) {
+      middle(t, 0, sb, sa, pa, pb);
+#pragma unroll
+      for (int i = 0; i < kKT / 32; ++i) sb[i] = sa[i];
+#pragma unroll
+      for (int i = 0; i < kKT / 16; ++i) pa[i] = pb[i];
+      ++t;
+    }
+    // The last tile: no tile after it to start.
+    step_barrier();
+    load_v(t);
+    clear_v(t - 1);
+    mask(t, sb);
+    run(Qk(), All(), Yes(), 0, (t - 1) & 1, sb, sa, pa, pb);
+    finish(t, sb);
+#pragma unroll
+    for (int i = 0; i < kKT / 16; ++i) pa[i] = pb[i];
   }
+  step_barrier();
+  clear_v(n_tiles - 1);
+  run(Qk(), All(), No(), 0, (n_tiles - 1) & 1, sb, sa, pa, pb);
 
   float l = sum_xor32(lrow);
   const float tm = sum_xor32(trow);

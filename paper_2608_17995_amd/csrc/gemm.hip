@@ -4,8 +4,8 @@
 // bf16 path (MFMA):
 //  - Macro tile 256 x BN (BN in {256, 192, 128}) x 64, one 512-thread
 //    workgroup of 8 waves (2 x 4, or 4 x 2 for BN = 192), each wave a
-//    128 x 64 (64 x 96) block of v_mfma_f32_32x32x16_bf16 tiles; two
-//    waves per SIMD hide each other's LDS and barrier waits.  The 256-wide
+//    128 x 64 (64 x 96) block of v_mfma_f32_32x32x16_bf16 tiles (16x16x32 in
+//    the ping-pong kernel); two waves per SIMD hide each other's LDS and barrier waits.  The 256-wide
 //    tile runs the ping-pong form (gemm_bf16_pp_kernel): the two halves of
 //    the workgroup alternate compute and memory phases.
 //  - The MFMA computes C^T = W A^T, so each lane owns groups of four
@@ -622,14 +622,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(const
 // 8 rows of 128 bytes, or 4 columns of 256 bytes in a transposed region.  A
 // wave's LDS operations complete in order: no barrier.  The caller passes the
 // main loop's LDS once every wave is done with it.
-//   acc[i][j][4q + r] = C[row 32 i + l32][col 32 j + 8 q + 4 hi + r].
+//   acc[i][j][r] = C[row 16 i + l16][col 16 j + 4 g + r], l16 = lane % 16, g = lane / 16.
 // Row-major image: 128-byte rows, 16-byte chunk c of row r at chunk
-// c ^ ((r / 2) mod 8), its 8-byte halves exchanged when bit 4 of r is set:
-// the 8-byte accumulator writes (32 rows, one chunk) and the 16-byte row
-// reads are free of bank conflicts.
+// c ^ ((r / 2) mod 8): the 8-byte accumulator writes (16 rows, two halves of a
+// chunk) and the 16-byte row reads are free of bank conflicts.
 // Transposed image: 256-byte columns; lanes l, l ^ 1 first exchange half of
 // their four columns, so each holds two rows of two columns and writes
-// 4-byte row pairs; 16-byte chunk k of column c is at k ^ 4 ((c / 2) mod 4).
+// 4-byte row pairs; 16-byte chunk k of column c is at k ^ 2 ((c / 2) mod 8).
 // Split-K partials are stored as fp32 straight from the accumulators.
 // Every global access is a buffer access whose range (or an offset past it)
 // drops the rows >= M and the columns >= N: with plain accesses the bounds
@@ -645,11 +644,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const void* base, int64_t 
 
 template <int TM, int TN>
 __device__ __forceinline__ void pp_epilogue(GemmArgsPtr a, GemmProblemPtr p, int64_t m0, int64_t n0,
-                                            float* __restrict__ pbase, int64_t pld, const f32x16 (&acc)[TM][TN],
+                                            float* __restrict__ pbase, int64_t pld, const f32x4 (&acc)[TM][TN],
                                             u32x4* sm, int wave, int wm, int wn, int lane) {
-  constexpr int WM = 32 * TM, WN = 32 * TN;
+  constexpr int WM = 16 * TM, WN = 16 * TN;
   static_assert(WM == 128 && WN == 64, "LDS image");
-  const int l32 = lane % 32, hi = lane / 32;
+  const int l16 = lane % 16, g = lane / 16;
   const int64_t nb = n0 + wn * WN, mb = m0 + wm * WM, M = p->M, N = a->N;
   if (nb >= N || mb >= M) return;
   const int rows = int(std::min<int64_t>(WM, M - mb)), cols = int(std::min<int64_t>(WN, N - nb));
@@ -657,17 +656,11 @@ __device__ __forceinline__ void pp_epilogue(GemmArgsPtr a, GemmProblemPtr p, int
     const __amdgpu_buffer_rsrc_t r = buf(pbase + wm * WM * pld + wn * WN, rows * pld * 4);
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-      const uint32_t row = uint32_t(32 * i + l32) * uint32_t(pld * 4) + 16 * hi;
+      const uint32_t row = uint32_t(16 * i + l16) * uint32_t(pld * 4) + 16 * g;
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x16& c = acc[i][j];
-          const int n = 32 * j + 8 * q;  // cols is a multiple of 8 (split launches need N % 8 == 0)
-          const f32x4 w = {c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, w), r, int(n < cols ? row + 4 * n : kPast), 0,
-                                                 0);
-        }
+      for (int j = 0; j < TN; ++j)  // cols is a multiple of 8 (split launches need N % 8 == 0)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), r,
+                                               int(16 * j + 4 * g < cols ? row + 64 * j : kPast), 0, 0);
     }
     return;
   }
@@ -677,19 +670,17 @@ __device__ __forceinline__ void pp_epilogue(GemmArgsPtr a, GemmProblemPtr p, int
   bf16_t* out = static_cast<bf16_t*>(r0 ? p->out0 : r1 ? p->out1 : p->out2);
   const int64_t ldo = r0 ? p->ld0 : r1 ? p->ld1 : p->ld2;
   const int64_t col0 = nb - (r0 ? 0 : r1 ? n_split : n_split2);
-  // This lane's columns 32 j + 8 q + 4 hi .. + 3 of the strip (zeros past N).
-  auto load4 = [&](const void* base, u32x2 (&dst)[TN][4]) {
+  // This lane's columns 16 j + 4 g .. + 3 of the strip (zeros past N).
+  auto load4 = [&](const void* base, u32x2 (&dst)[TN]) {
     const __amdgpu_buffer_rsrc_t r = buf(static_cast<const bf16_t*>(base) + nb, base ? cols * 2 : 0);
 #pragma unroll
     for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        dst[j][q] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, 2 * (32 * j + 8 * q + 4 * hi), 0, 0));
+      dst[j] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, 2 * (16 * j + 4 * g), 0, 0));
   };
   auto f4 = [](const u32x2& w, int r) {
     return __uint_as_float(r & 1 ? w[r >> 1] & 0xffff0000u : w[r >> 1] << 16);
   };
-  u32x2 bias[TN][4];
+  u32x2 bias[TN];
   load4(p->bias, bias);
   char* reg = reinterpret_cast<char*>(sm) + wave * (WM * WN * 2);
   if (mode == EPI_STORE_T) {
@@ -697,24 +688,22 @@ __device__ __forceinline__ void pp_epilogue(GemmArgsPtr a, GemmProblemPtr p, int
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x16& c = acc[i][j];
-          const uint32_t p01 = pack_bf2(c[4 * q] + f4(bias[j][q], 0), c[4 * q + 1] + f4(bias[j][q], 1));
-          const uint32_t p23 = pack_bf2(c[4 * q + 2] + f4(bias[j][q], 2), c[4 * q + 3] + f4(bias[j][q], 3));
-          const uint32_t got = uint32_t(
-              __builtin_amdgcn_update_dpp(0, int(odd ? p01 : p23), kDppXor1, 0xf, 0xf, false));
-          const uint32_t lo = odd ? got : p01, up = odd ? p23 : got;  // rows l & ~1 and l | 1
-          const int cc = 32 * j + 8 * q + 4 * hi + 2 * int(odd);      // columns cc, cc + 1
-          const int chunk = (4 * i + (l32 >> 3)) ^ (((cc >> 1) & 3) << 2);
-          uint32_t* d = reinterpret_cast<uint32_t*>(reg + cc * (WM * 2) + chunk * 16) + ((l32 >> 1) & 3);
-          d[0] = __builtin_amdgcn_perm(up, lo, 0x05040100u);
-          d[WM * 2 / 4] = __builtin_amdgcn_perm(up, lo, 0x07060302u);
-        }
+      for (int j = 0; j < TN; ++j) {
+        const f32x4& c = acc[i][j];
+        const uint32_t p01 = pack_bf2(c[0] + f4(bias[j], 0), c[1] + f4(bias[j], 1));
+        const uint32_t p23 = pack_bf2(c[2] + f4(bias[j], 2), c[3] + f4(bias[j], 3));
+        const uint32_t got = uint32_t(
+            __builtin_amdgcn_update_dpp(0, int(odd ? p01 : p23), kDppXor1, 0xf, 0xf, false));
+        const uint32_t lo = odd ? got : p01, up = odd ? p23 : got;  // rows l & ~1 and l | 1
+        const int cc = 16 * j + 4 * g + 2 * int(odd);               // columns cc, cc + 1
+        const int chunk = (2 * i + (l16 >> 3)) ^ (((cc >> 1) & 7) << 1);
+        uint32_t* d = reinterpret_cast<uint32_t*>(reg + cc * (WM * 2) + chunk * 16) + ((l16 >> 1) & 3);
+        d[0] = __builtin_amdgcn_perm(up, lo, 0x05040100u);
+        d[WM * 2 / 4] = __builtin_amdgcn_perm(up, lo, 0x07060302u);
+      }
     const int k = lane % 16;
     auto column = [&](int cc) {
-      return *reinterpret_cast<const u32x4*>(reg + cc * (WM * 2) + (k ^ (((cc >> 1) & 3) << 2)) * 16);
+      return *reinterpret_cast<const u32x4*>(reg + cc * (WM * 2) + (k ^ (((cc >> 1) & 7) << 1)) * 16);
     };
     // Plain stores: a transposed row may start at any element.
     bf16_t* dst = out + col0 * ldo + mb;
@@ -739,13 +728,11 @@ __device__ __forceinline__ void pp_epilogue(GemmArgsPtr a, GemmProblemPtr p, int
   // Row-major: lane's 16-byte role is chunk lane % 8 of rows lane / 8 + 8 it.
   const int ch = lane % 8;
   auto chunk_at = [&](int row) { return reg + row * (WN * 2) + ((ch ^ ((row >> 1) & 7)) * 16); };
-  auto half_at = [&](int row, int c) {  // 8-byte half hi of chunk c
-    return reg + row * (WN * 2) + ((c ^ ((row >> 1) & 7)) * 16) + 8 * (hi ^ ((row >> 4) & 1));
+  auto half_at = [&](int row, int j) {  // this lane's four columns of column tile j
+    return reg + row * (WN * 2) + (((2 * j + (g >> 1)) ^ ((row >> 1) & 7)) * 16) + 8 * (g & 1);
   };
-  // Rows lane / 8 + 8 it: bit 4 of the row is bit 1 of it.
-  auto halves = [](const u32x4& w, int it) { return it & 2 ? u32x4{w[2], w[3], w[0], w[1]} : w; };
   const bool col_ok = 8 * ch < cols;
-  u32x2 gate[TN][4] = {};
+  u32x2 gate[TN] = {};
   if (mode == EPI_RESID_GATE) {
     // The residual goes through the same image, to meet the accumulators.
     load4(p->gate, gate);
@@ -759,29 +746,26 @@ __device__ __forceinline__ void pp_epilogue(GemmArgsPtr a, GemmProblemPtr p, int
       res[it] = __builtin_bit_cast(
           u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, int(col_ok ? off + it * uint32_t(ldr * 16) : kPast), 0, 0));
 #pragma unroll
-    for (int it = 0; it < WM / 8; ++it) *reinterpret_cast<u32x4*>(chunk_at(lane / 8 + 8 * it)) = halves(res[it], it);
+    for (int it = 0; it < WM / 8; ++it) *reinterpret_cast<u32x4*>(chunk_at(lane / 8 + 8 * it)) = res[it];
   }
   auto convert = [&](auto mode_tag) {
     constexpr int kMode = decltype(mode_tag)::value;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < TN; ++j) {
+        u32x2* d = reinterpret_cast<u32x2*>(half_at(16 * i + l16, j));
+        u32x2 rw;
+        if constexpr (kMode == EPI_RESID_GATE) rw = *d;
+        float v[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x16& c = acc[i][j];
-          u32x2* d = reinterpret_cast<u32x2*>(half_at(32 * i + l32, 4 * j + q));
-          u32x2 rw;
-          if constexpr (kMode == EPI_RESID_GATE) rw = *d;
-          float v[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            v[r] = c[4 * q + r] + f4(bias[j][q], r);
-            if constexpr (kMode == EPI_GELU) v[r] = gelu_fast(v[r]);
-            if constexpr (kMode == EPI_RESID_GATE) v[r] = f4(rw, r) + f4(gate[j][q], r) * v[r];
-          }
-          *d = u32x2{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])};
+        for (int r = 0; r < 4; ++r) {
+          v[r] = acc[i][j][r] + f4(bias[j], r);
+          if constexpr (kMode == EPI_GELU) v[r] = gelu_fast(v[r]);
+          if constexpr (kMode == EPI_RESID_GATE) v[r] = f4(rw, r) + f4(gate[j], r) * v[r];
         }
+        *d = u32x2{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])};
+      }
   };
   if (mode == EPI_GELU) convert(std::integral_constant<int, EPI_GELU>());
   else if (mode == EPI_RESID_GATE) convert(std::integral_constant<int, EPI_RESID_GATE>());
@@ -790,7 +774,7 @@ __device__ __forceinline__ void pp_epilogue(GemmArgsPtr a, GemmProblemPtr p, int
   const uint32_t off = uint32_t(lane / 8) * uint32_t(ldo * 2) + 16 * ch;
 #pragma unroll
   for (int it = 0; it < WM / 8; ++it) {
-    const u32x4 w = halves(*reinterpret_cast<const u32x4*>(chunk_at(lane / 8 + 8 * it)), it);
+    const u32x4 w = *reinterpret_cast<const u32x4*>(chunk_at(lane / 8 + 8 * it));
     __builtin_amdgcn_raw_buffer_store_b128(w, r, int(col_ok ? off + it * uint32_t(ldo * 16) : kPast), 0, 0);
   }
   bf16_t* scat = static_cast<bf16_t*>(p->scat);
@@ -806,7 +790,7 @@ __device__ __forceinline__ void pp_epilogue(GemmArgsPtr a, GemmProblemPtr p, int
     }
 #pragma unroll
     for (int it = 0; it < WM / 8; ++it) {
-      const u32x4 w = halves(*reinterpret_cast<const u32x4*>(chunk_at(lane / 8 + 8 * it)), it);
+      const u32x4 w = *reinterpret_cast<const u32x4*>(chunk_at(lane / 8 + 8 * it));
       if (at[it] >= 0 && at[it] < scat_n) *reinterpret_cast<u32x4*>(scat + at[it] * sld + col0 + 8 * ch) = w;
     }
   }
@@ -869,7 +853,7 @@ __device__ __forceinline__ PpTile pp_tile(uint32_t tn, uint32_t tm0, uint32_t tm
 // of four (one wave of each group per SIMD); group g owns output rows
 // [128 g, 128 g + 128) and each of its waves a 128 x 64 block.  A group
 // alternates a memory phase (read the fragments of a whole k-tile from LDS
-// into registers, issue loads) with a compute phase (that k-tile's 32 MFMAs
+// into registers, issue loads) with a compute phase (that k-tile's 64 MFMAs
 // and nothing else), one workgroup barrier per phase, the groups one phase
 // apart: each SIMD's matrix pipe is fed by one wave while the other does the
 // memory work.
@@ -884,20 +868,22 @@ __device__ __forceinline__ PpTile pp_tile(uint32_t tn, uint32_t tm0, uint32_t tm
 // phase 2t + 1: every load is issued in a memory phase, each memory phase
 // issues the same eight per wave, and each load has at least two phases
 // (about 2000 cycles) before a barrier that waits for it.
-// Bound by: the clock under full matrix load.  The MFMAs alone (nothing loaded
-// or read) take 1.15 us per k-tile on 252 CUs and 0.9 on 144, this loop 1.42
-// and 0.92.  Measured (bias epilogue, TFLOP/s, before -> now; before: tiles
-// staged through registers and fragments read between the MFMAs): 1741 x 9216
-// x 3072 1023 -> 1250, 16896 x 12288 x 3072 1020 -> 1350, 8192^3 1090 -> 1458
-// (the vendor library: 1150, 1352, 1409).  Two tiles of each operand with all
-// loads in one phase ran 5 % slower at M = 1741 (the load unit needs 16
-// cycles per 1 KB load, a whole phase for a tile, and group 1's MFMAs queued
-// behind its loads); half k-tiles per phase (twice the barriers) 8 % slower;
-// without the raised priority in the compute phase 4-8 % slower.
+// Bound by: the clock under full matrix load (1.55 GHz measured, matrix pipe
+// 78 % busy).  Hence the 16x16x32 products: alone, on all CUs, they sustain
+// 2036 TFLOP/s where 32x32x16 sustain 1806 (a smaller accumulator is read and
+// written per operation).  Measured (bias epilogue, TFLOP/s, before: tiles
+// staged through registers, fragments read between the MFMAs; then on 32x32x16;
+// now): 1741 x 9216 x 3072 1023 -> 1250 -> 1329, 16896 x 12288 x 3072 1020 ->
+// 1350 -> 1446, 8192^3 1090 -> 1458 -> 1552 (the vendor library: 1150, 1352,
+// 1409).  Two tiles of each operand with all loads in one phase ran 5 % slower
+// at M = 1741 (the load unit needs 16 cycles per 1 KB load, a whole phase for
+// a tile, and group 1's MFMAs queued behind its loads); half k-tiles per phase
+// (twice the barriers) 8 % slower; without the raised priority in the compute
+// phase 4-8 % slower.
 __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmArgs args, float* __restrict__ partial,
                                                           int splits, int tail, int tsp) {
   constexpr int BN = 256, WM = 128, WN = 64;
-  constexpr int TM = WM / 32, TN = WN / 32;
+  constexpr int TM = WM / 16, TN = WN / 16;
   constexpr int kOp = kBM * 8;               // 16-byte chunks of one operand's k-tile
   // Two A buffers, then three W buffers (32 KB each): all 160 KB of the CU.
   __shared__ u32x4 lds[5 * kOp];
@@ -916,7 +902,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmArgs args, 
   const bf16_t* W = static_cast<const bf16_t*>(p->W);
   const int tid = threadIdx.x, lane = tid % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int l32 = lane % 32, hi = lane / 32;
+  const int l16 = lane % 16, g = lane / 16;
   const int grp = wave / 4;
   const int wm = grp, wn = wave % 4;
 
@@ -966,28 +952,26 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmArgs args, 
     for (int j = 0; j < 4; ++j) lds_load16(w_dst + ws * (kOp * 16), w_off[j], r, koff, 4096 * j);
   };
 
-  f32x16 acc[TM][TN];
+  f32x4 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // The fragments of a whole k-tile: read in one phase, multiplied in the next.
-  constexpr int KS = kBK / 16;
+  constexpr int KS = kBK / 32;
   bf16x8 af[KS][TM], wf[KS][TN];
-  const int sw = (l32 >> 1) & 7;
-  const u32x4* La = lds + (wm * WM + l32) * 8;
-  const u32x4* Lw = lds + 2 * kOp + (wn * WN + l32) * 8;
+  const int sw = (l16 >> 1) & 7;
+  const u32x4* La = lds + (wm * WM + l16) * 8;
+  const u32x4* Lw = lds + 2 * kOp + (wn * WN + l16) * 8;
   auto read = [&](int t, int ws) {
 #pragma unroll
     for (int k = 0; k < KS; ++k) {
-      const int c = (2 * k + hi) ^ sw;
+      const int c = (4 * k + g) ^ sw;
 #pragma unroll
-      for (int j = 0; j < TN; ++j) wf[k][j] = as_bf16x8(Lw[ws * kOp + 256 * j + c]);
+      for (int j = 0; j < TN; ++j) wf[k][j] = as_bf16x8(Lw[ws * kOp + 128 * j + c]);
 #pragma unroll
-      for (int i = 0; i < TM; ++i) af[k][i] = as_bf16x8(La[(t & 1) * kOp + 256 * i + c]);
+      for (int i = 0; i < TM; ++i) af[k][i] = as_bf16x8(La[(t & 1) * kOp + 128 * i + c]);
     }
   };
   auto mul = [&]() {
@@ -997,7 +981,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmArgs args, 
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = mfma32x32x16(wf[k][j], af[k][i], acc[i][j]);
+        for (int j = 0; j < TN; ++j) acc[i][j] = mfma16x16x32(wf[k][j], af[k][i], acc[i][j]);
     __builtin_amdgcn_s_setprio(0);
   };
   auto bar = [&]() {
