@@ -3,8 +3,18 @@
 //
 // bf16: one 256-thread workgroup per (128 query rows, head), 32 rows per
 // wave, two workgroups per CU, the row blocks of one head on one XCD.  Key
-// tiles of 64 rows and the matching V^T tile are prefetched into registers
-// one tile ahead and staged in padded LDS.
+// tiles of 64 rows and the matching V^T tiles go from memory to LDS directly,
+// two tiles of each in flight or in use.  The products of a step (P(t - 1) V
+// and S(t + 1) = K Q^T) do not depend on its softmax (of S(t)), so a wave
+// issues them interleaved, in a fixed order: the matrix pipe runs under the
+// exponentials.
+// Bound by: the matrix pipe at the clock that full load leaves (1.65 GHz
+// measured): without the softmax the same loop takes 2.43 ms at S = 16896, 24
+// heads, without fragment reads 2.83, whole 3.15 (1110 TFLOP/s).  Measured
+// before -> now (tiles staged through registers, the softmax between the two
+// products): S = 16896 3.71 -> 3.15 ms, 5171 414 -> 345 us, the masked pass of
+// S = 2457 119 -> 104 us.  On 16x16x32 products, which the GEMM prefers, 3.28 ms:
+// twice the instructions compete with the softmax for issue.
 // Both products run on v_mfma_f32_32x32x16_bf16 in transposed form:
 //   S^T = K Q^T   -> each lane holds 16 keys x 1 query row (row = lane % 32),
 //   O^T = V^T P^T -> each lane holds 16 head-dim values of the same row,
@@ -173,7 +183,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const AttnArgs a) {
   constexpr int kKC = DH / 8;                // 16-byte chunks per K row
   constexpr int kKR = kWave / kKC;           // K rows per load instruction
   constexpr int kKB = kKT * DH * 2, kVB = DH * kKT * 2;  // bytes of a K and a V^T tile
-  constexpr int kKL = kKB / 1024 / NW, kVL = kVB / 1024 / NW;  // load instructions per wave and tile
+  constexpr int kKL = kKB / 1024 / NW, kVL = WITH_V ? kVB / 1024 / NW : 0;  // load instructions per wave and tile
   // Two K tiles, then two V^T tiles, without padding: 16-byte chunk c of K row
   // r is at c ^ (r mod 16) (128-byte rows, DH = 64: c ^ (r / 2 mod 8)), of
   // V^T row r at c ^ (r / 2 mod 8): the fragment reads are conflict-free.
@@ -207,7 +217,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const AttnArgs a) {
   // Staging: a load instruction moves 1 KB straight to LDS (lane-linear, so
   // the swizzle and the key permutation are applied to each lane's source).
   auto swz_k = [](int r) { return DH == 128 ? r & 15 : (r >> 1) & 7; };
-  uint32_t k_off[kKL], v_off[kVL];
+  uint32_t k_off[kKL], v_off[kVL > 0 ? kVL : 1];
 #pragma unroll
   for (int j = 0; j < kKL; ++j) {
     const int r = kKR * (wave + NW * j) + lane / kKC;
@@ -270,25 +280,27 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const AttnArgs a) {
   typedef f32x16 STile[kKT / 32];
   typedef bf16x8 PTile[kKT / 16];
   constexpr int kQK = kC * (kKT / 32), kPV = WITH_V ? kDT * (kKT / 16) : 0;
-  constexpr int kRd = 4;  // fragments read ahead of their product
-  // Products 0 .. kQK - 1 of a step are those of S = K Q^T (two independent
-  // chains), the next kPV those of O^T += V^T P^T (kDT chains).
+    constexpr int kRd = 4;  // fragments read ahead of their product
+  // Slots 0 .. kPV - 1 of a step are the V^T fragments of O^T += V^T P^T (kDT
+  // independent chains), the next kQK the K fragments of S = K Q^T (two).  In
+  // this order S(t + 1) and P(t) take over registers that S(t) and P(t - 1)
+  // leave: 227 of the 256, where the other order needed 248.
   auto fragment = [&](int i, int kbuf, int vbuf) {
-    if (i < kQK) {
-      const int c = i / 2, t = i % 2;
+    if (i >= kPV) {
+      const int c = (i - kPV) / 2, t = (i - kPV) % 2;
       return as_bf16x8(*reinterpret_cast<const u32x4*>(smem + kbuf * kKB + (l32 + 32 * t) * (DH * 2) +
                                                        ((2 * c) ^ sk) * 16));
     }
-    const int c = (i - kQK) / kDT, dt = (i - kQK) % kDT;
+    const int c = i / kDT, dt = i % kDT;
     return as_bf16x8(*reinterpret_cast<const u32x4*>(smem + 2 * kKB + vbuf * kVB + (l32 + 32 * dt) * (kKT * 2) +
                                                      ((2 * c) ^ sv) * 16));
   };
   auto product = [&](int i, const bf16x8& f, STile& sn, const PTile& pp) {
-    if (i < kQK) {
-      const int c = i / 2, t = i % 2;
+    if (i >= kPV) {
+      const int c = (i - kPV) / 2, t = (i - kPV) % 2;
       sn[t] = mfma32(f, qf[c], c == 0 ? f32x16{} : sn[t]);
     } else {
-      const int c = (i - kQK) / kDT, dt = (i - kQK) % kDT;
+      const int c = i / kDT, dt = i % kDT;
       oacc[dt] = mfma32(f, pp[c], oacc[dt]);
     }
   };
@@ -371,7 +383,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const AttnArgs a) {
       }
     }
   };
-  // Products [lo, up) of a step with the softmax of (s, p) spread over them
+  // Slots [lo, up) of a step with the softmax of (s, p) spread over them
   // (SOFTMAX), in this order: the compiler, left to itself, puts the products
   // first and the softmax after them, which serialises the two units.
   auto run = [&](auto lo_tag, auto up_tag, auto soft_tag, int kbuf, int vbuf, STile& s, STile& sn, const PTile& pp,
@@ -397,7 +409,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const AttnArgs a) {
   using Yes = std::integral_constant<bool, true>;
   using No = std::integral_constant<bool, false>;
   using Zero = std::integral_constant<int, 0>;
-  using Qk = std::integral_constant<int, kQK>;
+  using Pv = std::integral_constant<int, kPV>;
   using All = std::integral_constant<int, kQK + kPV>;
   // V^T columns of tile `it` that do not count become zeros (their
   // probabilities are 0, but the memory behind them may hold anything).
@@ -437,9 +449,12 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const AttnArgs a) {
   STile sa, sb;
   PTile pa, pb;
   load_k(0);
-  step_barrier();
-  if (n_tiles > 1) load_k(1);
-  run(Zero(), Qk(), No(), 0, 0, sb, sa, pa, pa);
+  load_k(1);
+  load_v(0);
+  if (n_tiles > 1) vm_wait<kKL + kVL>();
+  else vm_wait<kVL>();
+  lds_barrier();
+  run(Pv(), All(), No(), 0, 0, sb, sa, pa, pa);
   // The step's results are made in it, not sunk to where they are used.
   auto pin = [&](STile& sn, PTile& p) {
 #pragma unroll
@@ -464,9 +479,8 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const AttnArgs a) {
   };
   step_barrier();
   load_k(2);
-  load_v(0);
   mask(0, sa);
-  if (n_tiles > 1) run(Zero(), Qk(), No(), 1, 0, sb, sb, pa, pa);
+  if (n_tiles > 1) run(Pv(), All(), No(), 1, 0, sb, sb, pa, pa);
   run(Zero(), Zero(), Yes(), 0, 0, sa, sb, pa, pa);
   finish(0, sa);
   if (n_tiles > 1) {
@@ -488,14 +502,14 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const AttnArgs a) {
     load_v(t);
     clear_v(t - 1);
     mask(t, sb);
-    run(Qk(), All(), Yes(), 0, (t - 1) & 1, sb, sa, pa, pb);
+    run(Zero(), Pv(), Yes(), 0, (t - 1) & 1, sb, sa, pa, pb);
     finish(t, sb);
 #pragma unroll
     for (int i = 0; i < kKT / 16; ++i) pa[i] = pb[i];
   }
   step_barrier();
   clear_v(n_tiles - 1);
-  run(Qk(), All(), No(), 0, (n_tiles - 1) & 1, sb, sa, pa, pb);
+  run(Zero(), Pv(), No(), 0, (n_tiles - 1) & 1, sb, sa, pa, pb);
 
   float l = sum_xor32(lrow);
   const float tm = sum_xor32(trow);
