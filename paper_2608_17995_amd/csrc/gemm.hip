@@ -443,9 +443,9 @@ __device__ __forceinline__ void staged_epilogue(const GemmArgs& a, const GemmPro
 // Swizzled 16-byte chunk slot of (row, chunk) in a 128-byte LDS row.
 __device__ __forceinline__ int swz(int row, int chunk) { return row * 8 + (chunk ^ ((row >> 1) & 7)); }
 
-template <int BN, int WAVES_M, int WAVES_N, int STAGES>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(const GemmArgs a,
-                                                                           float* __restrict__ partial, int splits) {
+// The general kernel: 256 x 128 tiles, any alignment.
+__global__ __launch_bounds__(512) void gemm_bf16_kernel(const GemmArgs a, float* __restrict__ partial, int splits) {
+  constexpr int BN = 128, WAVES_M = 2, WAVES_N = 4;
   constexpr int NT = 64 * WAVES_M * WAVES_N;
   constexpr int WM = kBM / WAVES_M, WN = BN / WAVES_N;
   constexpr int TM = WM / 32, TN = WN / 32;  // 32x32 MFMA tiles per wave
@@ -542,71 +542,46 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(const
   };
 
   const int64_t n_t = kt1 - kt0;
-  if constexpr (STAGES == 2) {
-    // Software pipeline, two register stages and two LDS buffers: while
-    // k-tile t is multiplied from LDS, tile t + 1 (loaded one step earlier)
-    // is stored to the other buffer and tile t + 2 is in flight.  Loads
-    // complete in issue order, so "the older stage is ready" is
-    // vmcnt <= LPT while the newer stage is in flight, else vmcnt == 0.
-    Stage s0, s1;
-    if (n_t > 0) {
-      load_tile(s0, kt0);
-      if (n_t > 1) {
-        load_tile(s1, kt0 + 1);
-        vm_wait<LPT>();
-      } else {
-        vm_wait<0>();
-      }
+  // Software pipeline, two register stages and two LDS buffers: while
+  // k-tile t is multiplied from LDS, tile t + 1 (loaded one step earlier)
+  // is stored to the other buffer and tile t + 2 is in flight.  Loads
+  // complete in issue order, so "the older stage is ready" is
+  // vmcnt <= LPT while the newer stage is in flight, else vmcnt == 0.
+  Stage s0, s1;
+  if (n_t > 0) {
+    load_tile(s0, kt0);
+    if (n_t > 1) {
+      load_tile(s1, kt0 + 1);
+      vm_wait<LPT>();
+    } else {
+      vm_wait<0>();
+    }
+    ready(s0);
+    store_tile(s0, 0);
+  }
+  lds_barrier();
+  for (int64_t t = 0; t < n_t; t += 2) {
+    // even step: compute buffer 0; s1 holds tile t + 1.
+    const bool next2 = t + 2 < n_t;
+    if (next2) load_tile(s0, kt0 + t + 2);
+    compute(0);
+    if (t + 1 < n_t) {
+      if (next2) vm_wait<LPT>(); else vm_wait<0>();
+      ready(s1);
+      store_tile(s1, 1);
+    }
+    lds_barrier();
+    if (t + 1 >= n_t) break;
+    // odd step: compute buffer 1; s0 holds tile t + 2.
+    const bool next3 = t + 3 < n_t;
+    if (next3) load_tile(s1, kt0 + t + 3);
+    compute(1);
+    if (next2) {
+      if (next3) vm_wait<LPT>(); else vm_wait<0>();
       ready(s0);
       store_tile(s0, 0);
     }
     lds_barrier();
-    for (int64_t t = 0; t < n_t; t += 2) {
-      // even step: compute buffer 0; s1 holds tile t + 1.
-      const bool next2 = t + 2 < n_t;
-      if (next2) load_tile(s0, kt0 + t + 2);
-      compute(0);
-      if (t + 1 < n_t) {
-        if (next2) vm_wait<LPT>(); else vm_wait<0>();
-        ready(s1);
-        store_tile(s1, 1);
-      }
-      lds_barrier();
-      if (t + 1 >= n_t) break;
-      // odd step: compute buffer 1; s0 holds tile t + 2.
-      const bool next3 = t + 3 < n_t;
-      if (next3) load_tile(s1, kt0 + t + 3);
-      compute(1);
-      if (next2) {
-        if (next3) vm_wait<LPT>(); else vm_wait<0>();
-        ready(s0);
-        store_tile(s0, 0);
-      }
-      lds_barrier();
-    }
-  } else {
-    // One register stage, two LDS buffers: tile t + 1 is in flight while
-    // tile t is multiplied.
-    Stage st;
-    if (n_t > 0) {
-      load_tile(st, kt0);
-      vm_wait<0>();
-      ready(st);
-      store_tile(st, 0);
-    }
-    lds_barrier();
-    for (int64_t t = 0; t < n_t; ++t) {
-      const int buf = int(t & 1);
-      const bool next = t + 1 < n_t;
-      if (next) load_tile(st, kt0 + t + 1);
-      compute(buf);
-      if (next) {
-        vm_wait<0>();
-        ready(st);
-        store_tile(st, buf ^ 1);
-      }
-      lds_barrier();
-    }
   }
 
   // The last barrier of the main loop has passed: LDS is free.
@@ -628,7 +603,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(const
 // chunk) and the 16-byte row reads are free of bank conflicts.
 // Transposed image: 256-byte columns; lanes l, l ^ 1 first exchange half of
 // their four columns, so each holds two rows of two columns and writes
-// 4-byte row pairs; 16-byte chunk k of column c is at k ^ 2 ((c / 2) mod 8).
+// 4-byte row pairs; 16-byte chunk k of column c is at k ^ 2 ((c / 2) mod 8)
+// (columns of 64 rows: mod 4).
 // Split-K partials are stored as fp32 straight from the accumulators.
 // Every global access is a buffer access whose range (or an offset past it)
 // drops the rows >= M and the columns >= N: with plain accesses the bounds
@@ -647,7 +623,7 @@ __device__ __forceinline__ void pp_epilogue(GemmArgsPtr a, GemmProblemPtr p, int
                                             float* __restrict__ pbase, int64_t pld, const f32x4 (&acc)[TM][TN],
                                             u32x4* sm, int wave, int wm, int wn, int lane) {
   constexpr int WM = 16 * TM, WN = 16 * TN;
-  static_assert(WM == 128 && WN == 64, "LDS image");
+  static_assert((WM == 128 || WM == 64) && WN == 64, "LDS image");
   const int l16 = lane % 16, g = lane / 16;
   const int64_t nb = n0 + wn * WN, mb = m0 + wm * WM, M = p->M, N = a->N;
   if (nb >= N || mb >= M) return;
@@ -685,6 +661,7 @@ __device__ __forceinline__ void pp_epilogue(GemmArgsPtr a, GemmProblemPtr p, int
   char* reg = reinterpret_cast<char*>(sm) + wave * (WM * WN * 2);
   if (mode == EPI_STORE_T) {
     const bool odd = lane & 1;
+    auto swz_t = [](int cc) { return ((cc >> 1) & (WM / 16 - 1)) << 1; };
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -696,27 +673,28 @@ __device__ __forceinline__ void pp_epilogue(GemmArgsPtr a, GemmProblemPtr p, int
             __builtin_amdgcn_update_dpp(0, int(odd ? p01 : p23), kDppXor1, 0xf, 0xf, false));
         const uint32_t lo = odd ? got : p01, up = odd ? p23 : got;  // rows l & ~1 and l | 1
         const int cc = 16 * j + 4 * g + 2 * int(odd);               // columns cc, cc + 1
-        const int chunk = (2 * i + (l16 >> 3)) ^ (((cc >> 1) & 7) << 1);
+        const int chunk = (2 * i + (l16 >> 3)) ^ swz_t(cc);
         uint32_t* d = reinterpret_cast<uint32_t*>(reg + cc * (WM * 2) + chunk * 16) + ((l16 >> 1) & 3);
         d[0] = __builtin_amdgcn_perm(up, lo, 0x05040100u);
         d[WM * 2 / 4] = __builtin_amdgcn_perm(up, lo, 0x07060302u);
       }
-    const int k = lane % 16;
+    constexpr int kCh = WM / 8;                 // 16-byte chunks per column
+    const int k = lane % kCh;
     auto column = [&](int cc) {
-      return *reinterpret_cast<const u32x4*>(reg + cc * (WM * 2) + (k ^ (((cc >> 1) & 7) << 1)) * 16);
+      return *reinterpret_cast<const u32x4*>(reg + cc * (WM * 2) + (k ^ swz_t(cc)) * 16);
     };
     // Plain stores: a transposed row may start at any element.
     bf16_t* dst = out + col0 * ldo + mb;
     const bool whole = 8 * k + 8 <= rows;
 #pragma unroll
-    for (int it = 0; it < WN / 4; ++it) {
-      const int cc = lane / 16 + 4 * it;
+    for (int it = 0; it < WN * kCh / kWave; ++it) {
+      const int cc = lane / kCh + kWave / kCh * it;
       const u32x4 w = column(cc);
       if (whole && cc < cols) *reinterpret_cast<u32x4*>(dst + cc * ldo + 8 * k) = w;
     }
     if (rows % 8 != 0 && k == rows / 8) {  // the last, partial group of eight rows
 #pragma unroll 1
-      for (int cc = lane / 16; cc < cols; cc += 4) {
+      for (int cc = lane / kCh; cc < cols; cc += kWave / kCh) {
         const u32x4 w = column(cc);
 #pragma unroll
         for (int e = 0; e < 8; ++e)
@@ -733,9 +711,25 @@ __device__ __forceinline__ void pp_epilogue(GemmArgsPtr a, GemmProblemPtr p, int
   };
   const bool col_ok = 8 * ch < cols;
   u32x2 gate[TN] = {};
+  const bool images = mode == EPI_RESID_GATE && a->mod.B > 0;
+  const bf16_t* row_gate[TM];
   if (mode == EPI_RESID_GATE) {
-    // The residual goes through the same image, to meet the accumulators.
     load4(p->gate, gate);
+    if (images) {  // the segment of each of this lane's rows (see mod_offset), in a rolled loop: scalars are short
+      const int B = a->mod.B;
+      const int64_t row = p->row0 + mb, stride = a->mod.stride;
+      int seg[TM] = {};
+#pragma unroll 1
+      for (int k = 0; k < 2 * B - 1; ++k) {
+        const int64_t end = a->mod.end[k] - row;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) seg[i] += std::min(16 * i + l16, rows - 1) >= end ? 1 : 0;
+      }
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+        row_gate[i] = static_cast<const bf16_t*>(p->gate) + nb + (seg[i] < B ? seg[i] : seg[i] - B) * stride;
+    }
+    // The residual goes through the same image, to meet the accumulators.
     const int64_t ldr = p->ldr;
     const __amdgpu_buffer_rsrc_t r = buf(static_cast<const bf16_t*>(p->resid) + mb * ldr + col0,
                                          ((rows - 1) * ldr + cols) * 2);
@@ -756,7 +750,11 @@ __device__ __forceinline__ void pp_epilogue(GemmArgsPtr a, GemmProblemPtr p, int
       for (int j = 0; j < TN; ++j) {
         u32x2* d = reinterpret_cast<u32x2*>(half_at(16 * i + l16, j));
         u32x2 rw;
-        if constexpr (kMode == EPI_RESID_GATE) rw = *d;
+        if constexpr (kMode == EPI_RESID_GATE) {
+          rw = *d;
+          // Per-image gates: this row's (columns past N read as another's, unused).
+          if (images) gate[j] = *reinterpret_cast<const u32x2*>(row_gate[i] + std::min(16 * j + 4 * g, cols - 4));
+        }
         float v[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -804,51 +802,22 @@ __device__ __forceinline__ void pp_epilogue(GemmArgsPtr a, GemmProblemPtr p, int
 // kBand row tiles and 4 weight tiles in its L2 (walking down all the rows
 // of a long problem re-read A once per column of tiles).
 constexpr uint32_t kBand = 8;
-struct PpTile {
-  int prob, tm, tn, ks, tidx;
-};
-__device__ __forceinline__ void pp_place(uint32_t id, uint32_t tn, uint32_t tm0, uint32_t tm1, PpTile& t) {
-  t.prob = id >= tn * tm0;
-  const uint32_t local = t.prob ? id - tn * tm0 : id, tm = t.prob ? tm1 : tm0;
+__device__ __forceinline__ void pp_place(uint32_t id, uint32_t tn, uint32_t tm0, uint32_t tm1, int& prob, int& row,
+                                         int& col) {
+  prob = id >= tn * tm0;
+  const uint32_t local = prob ? id - tn * tm0 : id, tm = prob ? tm1 : tm0;
   const uint32_t bands = (tm + kBand - 1) / kBand, small = tm / bands, big = tm % bands;  // `big` bands of small + 1
   const uint32_t in_big = big * (small + 1) * tn;
   const bool first = local < in_big;
   const uint32_t rows = first ? small + 1 : small, u = first ? local : local - in_big;
   const uint32_t band = u / (rows * tn), v = u % (rows * tn);
-  t.tm = int((first ? 0 : big * (small + 1)) + band * rows + v % rows);
-  t.tn = int(v / rows);
+  row = int((first ? 0 : big * (small + 1)) + band * rows + v % rows);
+  col = int(v / rows);
 }
 __device__ __forceinline__ uint32_t xcd_logical_id32(uint32_t bid, uint32_t grid) {
   const uint32_t per = grid / 8, rem = grid % 8, x = bid % 8, i = bid / 8;
   return x * per + std::min(x, rem) + i;
 }
-// Workgroup -> tile, k split and (for a split-tail tile) its index in the
-// tail, -1 otherwise.  The k splits of a tile are adjacent ids.  Split tail:
-// when the tiles overrun the last full round of workgroups by a few, the
-// first tiles run whole and the last `tail` ones in `tsp` k splits each, in
-// the workgroups dispatched after the whole tiles: the partial round takes
-// 1 / tsp of a tile's time.  The two classes are renumbered for the XCDs
-// separately.
-__device__ __forceinline__ PpTile pp_tile(uint32_t tn, uint32_t tm0, uint32_t tm1, uint32_t splits, uint32_t tail,
-                                          uint32_t tsp) {
-  PpTile t;
-  uint32_t id;
-  const uint32_t bid = blockIdx.x, whole = tail ? tn * (tm0 + tm1) - tail : gridDim.x;
-  if (bid < whole) {
-    const uint32_t u = xcd_logical_id32(bid, whole);
-    id = u / splits;
-    t.ks = int(u % splits);
-    t.tidx = -1;
-  } else {
-    const uint32_t u = xcd_logical_id32(bid - whole, gridDim.x - whole);
-    t.tidx = int(u / tsp);
-    t.ks = int(u % tsp);
-    id = whole + u / tsp;
-  }
-  pp_place(id, tn, tm0, tm1, t);
-  return t;
-}
-
 // Ping-pong form of the 256 x 256 x 64 kernel.  The 8 waves form two groups
 // of four (one wave of each group per SIMD); group g owns output rows
 // [128 g, 128 g + 128) and each of its waves a 128 x 64 block.  A group
@@ -880,173 +849,209 @@ __device__ __forceinline__ PpTile pp_tile(uint32_t tn, uint32_t tm0, uint32_t tm
 // a tile, and group 1's MFMAs queued behind its loads); half k-tiles per phase
 // (twice the barriers) 8 % slower; without the raised priority in the compute
 // phase 4-8 % slower.
+template <int BN>
 __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmArgs args, float* __restrict__ partial,
-                                                          int splits, int tail, int tsp) {
-  constexpr int BN = 256, WM = 128, WN = 64;
-  constexpr int TM = WM / 16, TN = WN / 16;
-  constexpr int kOp = kBM * 8;               // 16-byte chunks of one operand's k-tile
-  // Two A buffers, then three W buffers (32 KB each): all 160 KB of the CU.
-  __shared__ u32x4 lds[5 * kOp];
+                                                          int units, int splits, int tail, int tsp) {
+  constexpr int WM = BN / 2, WN = 64;        // a wave's block; a group's four waves cover 128 x BN
+  constexpr int TM = WM / 16, TN = WN / 16, kWN = BN / WN;
+  constexpr int RA = BN == 256 ? 2 : 3, RW = RA + 1;   // tiles of A and W in LDS
+  constexpr int kA = kBM * 8, kW = BN * 8;   // 16-byte chunks of one operand's k-tile
+  constexpr int LA = 4, LW = BN / 64;        // load instructions per wave for half an A and half a W tile
+  __shared__ u32x4 lds[RA * kA + RW * kW];   // all 160 KB
+  static_assert(sizeof(lds) == 160 * 1024, "LDS");
 
   // The arguments through the kernel-argument segment: a problem picked by a
   // uniform index stays scalar loads (a copy would live in private memory).
   const GemmArgsPtr a = (GemmArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
-  const int tn = int((a->N + BN - 1) / BN);
-  const int tm0 = int((a->p[0].M + kBM - 1) / kBM), tm1 = a->nprob > 1 ? int((a->p[1].M + kBM - 1) / kBM) : 0;
-  const PpTile tile = pp_tile(tn, tm0, tm1, splits, tail, tsp);
-  const int prob = tile.prob, ks = tile.ks, tidx = tile.tidx;
-  const GemmProblemPtr p = &a->p[prob];
-  const int64_t m0 = int64_t(tile.tm) * kBM, n0 = int64_t(tile.tn) * BN;
-  const int64_t M = p->M, N = a->N, K = a->K, lda = p->lda;
-  const bf16_t* A = static_cast<const bf16_t*>(p->A);
-  const bf16_t* W = static_cast<const bf16_t*>(p->W);
-  const int tid = threadIdx.x, lane = tid % kWave;
+  const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int l16 = lane % 16, g = lane / 16;
-  const int grp = wave / 4;
-  const int wm = grp, wn = wave % 4;
-
-  const int nsp = tidx >= 0 ? tsp : splits;
-  const int nk = int(K / kBK);
-  const int kt0 = nk * ks / nsp, kt1 = nk * (ks + 1) / nsp;
-  const int n_t = kt1 - kt0;
-
-  // Staging: one load instruction moves 8 rows of 128 bytes; the LDS side is
-  // lane-linear, so the swizzle is applied to the chunk each lane fetches.
-  // Wave wn of a group moves rows 8 wn + 32 j (j = 0..3) of a 128-row half
-  // (one swizzle for all j): group 0 the second half of A and the first half
-  // of W, group 1 the first half of A and the second half of W.
-  const int row_t = wn * 8 + lane / 8;
-  const int kc_t = (lane % 8) ^ ((row_t >> 1) & 7);
-  const int a_half = 128 * (1 - grp), w_half = 128 * grp;
-  uint32_t a_off[4], w_off[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    a_off[j] = uint32_t(((a_half + row_t + 32 * j) * lda + kc_t * 8) * 2);
-    w_off[j] = uint32_t(((w_half + row_t + 32 * j) * K + kc_t * 8) * 2);
-  }
-  auto uniform = [](u32x4 r) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) r[e] = __builtin_amdgcn_readfirstlane(r[e]);
-    return r;
-  };
-  const u32x4 ra = uniform(buffer_rsrc(A + m0 * lda, range32((M - m0) * lda * 2)));
-  const u32x4 rw = uniform(buffer_rsrc(W + n0 * K, range32((N - n0) * K * 2)));
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(uint32_t(reinterpret_cast<uintptr_t>(
       (__attribute__((address_space(3))) char*)(&lds[0]))));
-  const uint32_t a_dst = lds0 + a_half * 128 + wn * 1024;
-  const uint32_t w_dst = lds0 + 2 * kOp * 16 + w_half * 128 + wn * 1024;
-  // This wave's share of k-tile t of A (buffer t mod 2) or W (slot ws).  Past
-  // the last k-tile the resource's range is 0: no memory is read, and the
-  // loads still count, so every wait below is the same constant.
-  auto load_a = [&](int t) {
-    const uint32_t koff = uint32_t(kt0 + t) * (kBK * 2);
-    const u32x4 r = {ra[0], ra[1], t < n_t ? ra[2] : 0u, ra[3]};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) lds_load16(a_dst + (t & 1) * (kOp * 16), a_off[j], r, koff, 4096 * j);
-  };
-  auto load_w = [&](int t, int ws) {
-    const uint32_t koff = uint32_t(kt0 + t) * (kBK * 2);
-    const u32x4 r = {rw[0], rw[1], t < n_t ? rw[2] : 0u, rw[3]};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) lds_load16(w_dst + ws * (kOp * 16), w_off[j], r, koff, 4096 * j);
-  };
-
-  f32x4 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // The fragments of a whole k-tile: read in one phase, multiplied in the next.
-  constexpr int KS = kBK / 32;
-  bf16x8 af[KS][TM], wf[KS][TN];
-  const int sw = (l16 >> 1) & 7;
-  const u32x4* La = lds + (wm * WM + l16) * 8;
-  const u32x4* Lw = lds + 2 * kOp + (wn * WN + l16) * 8;
-  auto read = [&](int t, int ws) {
-#pragma unroll
-    for (int k = 0; k < KS; ++k) {
-      const int c = (4 * k + g) ^ sw;
-#pragma unroll
-      for (int j = 0; j < TN; ++j) wf[k][j] = as_bf16x8(Lw[ws * kOp + 128 * j + c]);
-#pragma unroll
-      for (int i = 0; i < TM; ++i) af[k][i] = as_bf16x8(La[(t & 1) * kOp + 128 * i + c]);
-    }
-  };
-  auto mul = [&]() {
-    __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-    for (int k = 0; k < KS; ++k)
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = mfma16x16x32(wf[k][j], af[k][i], acc[i][j]);
-    __builtin_amdgcn_s_setprio(0);
-  };
   auto bar = [&]() {
     __builtin_amdgcn_sched_barrier(0);
     lds_barrier();
     __builtin_amdgcn_sched_barrier(0);
   };
 
-  // Each group runs its own straight loop; both pass the same barriers.
-  load_a(0);
-  load_w(0, 0);
-  int ws = 0, ws2 = 2;   // W slots of tiles t and t + 2
-  auto next_slot = [&]() {
-    ws2 = ws;
-    ws = ws == 2 ? 0 : ws + 1;
-  };
-  if (grp == 0) {
-    load_w(1, 1);
-    vm_wait<4>();
-    bar();
-    for (int t = 0; t < n_t; ++t) {
-      read(t, ws);
-      load_a(t + 1);
-      load_w(t + 2, ws2);
-      vm_wait<12>();   // phase 2t + 1 reads the A half loaded in phase 2t - 2
-      bar();
-      mul();
-      vm_wait<8>();    // phase 2t + 2 reads the W half loaded in phase 2t - 2
-      bar();
-      next_slot();
-    }
-    vm_wait<0>();
-    bar();
-  } else {
-    load_a(1);
-    load_w(1, 1);
-    vm_wait<8>();
-    bar();
-    if (n_t == 0) vm_wait<0>();
-    bar();
-    for (int t = 0; t < n_t; ++t) {
-      read(t, ws);
-      load_a(t + 2);
-      load_w(t + 2, ws2);
-      vm_wait<8>();    // phase 2t + 2 reads what phase 2t - 1 loaded
-      bar();
-      mul();
-      if (t == n_t - 1) vm_wait<0>();
-      bar();
-      next_slot();
-    }
-  }
+  // Work units in rounds of at most one per workgroup.  The units of a round
+  // are renumbered so that each XCD takes a contiguous range of them; the k
+  // splits of a tile are adjacent units.  Split tail: when the tiles overrun
+  // the last full round by a few, the first tiles run whole and the last
+  // `tail` ones in `tsp` k splits each, as units of their own in a round after
+  // the whole tiles.
+  const uint32_t tn_all = uint32_t((a->N + BN - 1) / BN), tm0 = uint32_t((a->p[0].M + kBM - 1) / kBM);
+  const uint32_t tm1 = a->nprob > 1 ? uint32_t((a->p[1].M + kBM - 1) / kBM) : 0u;
+  const uint32_t whole = tail ? tn_all * (tm0 + tm1) - uint32_t(tail) : uint32_t(units);
+  for (uint32_t unit0 = 0; unit0 < uint32_t(units);) {
+    const uint32_t end = std::min(unit0 < whole ? whole : uint32_t(units), unit0 + gridDim.x);
+    const uint32_t here = unit0;
+    unit0 = end;
+    if (blockIdx.x >= end - here) continue;
+    // Per-lane values are made anew for each unit (hoisted out of this loop,
+    // they spilled).
+    int lane = tid % kWave, wave_u = wave;
+    asm volatile("" : "+v"(lane), "+s"(wave_u));
+    const int l16 = lane % 16, g = lane / 16;
+    const int grp = wave_u / 4, sub = wave_u % 4;
+    const int wm = grp * (128 / WM) + sub / kWN, wn = sub % kWN;
 
-  // Split partials: a tail tile's go to its own 256 x 256 block (split-major),
-  // a fully split launch's to rows of the [split][row][N] array.
-  float* pbase = nullptr;
-  int64_t pld = N;
-  if (tidx >= 0) {
-    pbase = partial + (int64_t(tidx) * tsp + ks) * (kBM * BN);
-    pld = BN;
-  } else if (splits > 1) {
-    const int64_t M0 = a->p[0].M, rows_all = M0 + (a->nprob > 1 ? a->p[1].M : 0);
-    pbase = partial + (ks * rows_all + (prob ? M0 : 0) + m0) * N + n0;
+    auto scalar = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    const uint32_t u = here + xcd_logical_id32(blockIdx.x, end - here);
+    const bool split_tail = u >= whole;
+    const uint32_t nsp = split_tail ? tsp : splits, v = split_tail ? u - whole : u;
+    const int ks = scalar(int(v % nsp)), tidx = split_tail ? scalar(int(v / nsp)) : -1;
+    int prob, tm, tn;
+    pp_place((split_tail ? whole : 0) + v / nsp, tn_all, tm0, tm1, prob, tm, tn);
+    prob = scalar(prob);
+    const GemmProblemPtr p = &a->p[prob];
+    const int64_t m0 = int64_t(scalar(tm)) * kBM, n0 = int64_t(scalar(tn)) * BN;
+    const int64_t M = p->M, N = a->N, K = a->K, lda = p->lda;
+    const bf16_t* A = static_cast<const bf16_t*>(p->A);
+    const bf16_t* W = static_cast<const bf16_t*>(p->W);
+    const int nk = int(K / kBK);
+    const int kt0 = scalar(nk * ks / int(nsp)), kt1 = scalar(nk * (ks + 1) / int(nsp));
+    const int n_t = kt1 - kt0;
+
+    // Staging: one load instruction moves 8 rows of 128 bytes; the LDS side is
+    // lane-linear, so the swizzle is applied to the chunk each lane fetches.
+    // Wave `sub` of a group moves rows 8 sub + 32 j of a half tile (one swizzle
+    // for all j): group 0 the second half of A and the first half of W,
+    // group 1 the first half of A and the second half of W.
+    const int row_t = sub * 8 + lane / 8;
+    const int kc_t = (lane % 8) ^ ((row_t >> 1) & 7);
+    const int a_half = 128 * (1 - grp), w_half = BN / 2 * grp;
+    uint32_t a_off[LA], w_off[LW];
+#pragma unroll
+    for (int j = 0; j < LA; ++j) a_off[j] = uint32_t(((a_half + row_t + 32 * j) * lda + kc_t * 8) * 2);
+#pragma unroll
+    for (int j = 0; j < LW; ++j) w_off[j] = uint32_t(((w_half + row_t + 32 * j) * K + kc_t * 8) * 2);
+    auto uniform = [](u32x4 r) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) r[e] = __builtin_amdgcn_readfirstlane(r[e]);
+      return r;
+    };
+    const u32x4 ra = uniform(buffer_rsrc(A + m0 * lda, range32((M - m0) * lda * 2)));
+    const u32x4 rw = uniform(buffer_rsrc(W + n0 * K, range32((N - n0) * K * 2)));
+    const uint32_t a_dst = lds0 + a_half * 128 + sub * 1024;
+    const uint32_t w_dst = lds0 + RA * kA * 16 + w_half * 128 + sub * 1024;
+    // This wave's share of k-tile t of A or W, into a slot of its ring.  Past
+    // the last k-tile the resource's range is 0: no memory is read, and the
+    // loads still count, so every wait below is the same constant.
+    auto load_a = [&](int t, int slot) {
+      const uint32_t koff = uint32_t(kt0 + t) * (kBK * 2);
+      const u32x4 r = {ra[0], ra[1], t < n_t ? ra[2] : 0u, ra[3]};
+#pragma unroll
+      for (int j = 0; j < LA; ++j) lds_load16(a_dst + slot * (kA * 16), a_off[j], r, koff, 4096 * j);
+    };
+    auto load_w = [&](int t, int slot) {
+      const uint32_t koff = uint32_t(kt0 + t) * (kBK * 2);
+      const u32x4 r = {rw[0], rw[1], t < n_t ? rw[2] : 0u, rw[3]};
+#pragma unroll
+      for (int j = 0; j < LW; ++j) lds_load16(w_dst + slot * (kW * 16), w_off[j], r, koff, 4096 * j);
+    };
+
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // The fragments of a whole k-tile: read in one phase, multiplied in the next.
+    constexpr int KS = kBK / 32;
+    bf16x8 af[KS][TM], wf[KS][TN];
+    const int sw = (l16 >> 1) & 7;
+    const u32x4* La = lds + (wm * WM + l16) * 8;
+    const u32x4* Lw = lds + RA * kA + (wn * WN + l16) * 8;
+    auto read = [&](int as, int ws) {
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        const int c = (4 * k + g) ^ sw;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) wf[k][j] = as_bf16x8(Lw[ws * kW + 128 * j + c]);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) af[k][i] = as_bf16x8(La[as * kA + 128 * i + c]);
+      }
+    };
+    auto mul = [&]() {
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int k = 0; k < KS; ++k)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] = mfma16x16x32(wf[k][j], af[k][i], acc[i][j]);
+      __builtin_amdgcn_s_setprio(0);
+    };
+
+    // Each group runs its own straight loop; both pass the same barriers.
+    // The slots of tiles t, t - 1 (= that of t + RA - 1, t + RW - 1) rotate.
+    constexpr int kStep = LA + LW;
+    int as = 0, ap = RA - 1, ws = 0, wp = RW - 1;
+    auto next = [&]() {
+      ap = as;
+      wp = ws;
+      as = as == RA - 1 ? 0 : as + 1;
+      ws = ws == RW - 1 ? 0 : ws + 1;
+    };
+    if (here > 0) bar();   // every wave is done with the last unit's epilogue
+    if (grp == 0) {
+      load_w(0, 0);
+#pragma unroll
+      for (int t = 0; t < RA - 1; ++t) {
+        load_a(t, t);
+        load_w(t + 1, t + 1);
+      }
+      vm_wait<(RA - 1) * kStep>();
+      bar();
+      for (int t = 0; t < n_t; ++t) {
+        read(as, ws);
+        load_a(t + RA - 1, ap);
+        load_w(t + RW - 1, wp);
+        vm_wait<LW + (RA - 1) * kStep>();   // the second half of A(t), which phase 2t + 1 reads
+        bar();
+        mul();
+        vm_wait<(RA - 1) * kStep>();        // the first half of W(t + 1), which phase 2t + 2 reads
+        bar();
+        next();
+      }
+      vm_wait<0>();
+      bar();
+    } else {
+#pragma unroll
+      for (int t = 0; t < RA; ++t) {
+        load_a(t, t);
+        load_w(t, t);
+      }
+      vm_wait<(RA - 1) * kStep>();
+      bar();
+      if (n_t == 0) vm_wait<0>();
+      bar();
+      for (int t = 0; t < n_t; ++t) {
+        read(as, ws);
+        load_a(t + RA, as);
+        load_w(t + RW - 1, wp);
+        vm_wait<(RA - 1) * kStep>();        // both halves of tile t + 1, which phase 2t + 2 reads
+        bar();
+        mul();
+        if (t == n_t - 1) vm_wait<0>();
+        bar();
+        next();
+      }
+    }
+
+    // Split partials: a tail tile's go to its own 256 x 256 block (split-major),
+    // a fully split launch's to rows of the [split][row][N] array.
+    float* pbase = nullptr;
+    int64_t pld = N;
+    if (tidx >= 0) {
+      pbase = partial + (int64_t(tidx) * tsp + ks) * (kBM * BN);
+      pld = BN;
+    } else if (splits > 1) {
+      const int64_t M0 = a->p[0].M, rows_all = M0 + (a->nprob > 1 ? a->p[1].M : 0);
+      pbase = partial + (ks * rows_all + (prob ? M0 : 0) + m0) * N + n0;
+    }
+    pp_epilogue<TM, TN>(a, p, m0, n0, pbase, pld, acc, lds, wave_u, wm, wn, lane);
   }
-  pp_epilogue<TM, TN>(a, p, m0, n0, pbase, pld, acc, lds, wave, wm, wn, lane);
 }
 
 // Sum the k splits of each tail tile in split order and apply the epilogue.
@@ -1060,10 +1065,10 @@ __global__ __launch_bounds__(256) void tail_reduce_kernel(const GemmArgs a, cons
   const int c = (int(threadIdx.x) % 32) * 8;
   const uint32_t tn = uint32_t((a.N + BN - 1) / BN), tm0 = uint32_t((a.p[0].M + kBM - 1) / kBM);
   const uint32_t tm1 = a.nprob > 1 ? uint32_t((a.p[1].M + kBM - 1) / kBM) : 0u;
-  PpTile pt;
-  pp_place(uint32_t(tn * (tm0 + tm1) - tail + t), tn, tm0, tm1, pt);
-  const GemmProblem p = pt.prob ? a.p[1] : a.p[0];
-  const int64_t m = int64_t(pt.tm) * kBM + r, n = int64_t(pt.tn) * BN + c;
+  int prob, row, col;
+  pp_place(uint32_t(tn * (tm0 + tm1) - tail + t), tn, tm0, tm1, prob, row, col);
+  const GemmProblem p = prob ? a.p[1] : a.p[0];
+  const int64_t m = int64_t(row) * kBM + r, n = int64_t(col) * BN + c;
   if (m >= p.M || n >= a.N) return;
   const float* src = partial + t * tsp * int64_t(kBM * BN) + r * BN + c;
   float v[8];
@@ -1162,7 +1167,7 @@ int64_t tiles_of(const GemmArgs& a, int bm, int bn) {
 // start anywhere.
 bool pp_layout_ok(const GemmArgs& a) {
   auto off = [](const void* ptr) { return reinterpret_cast<uintptr_t>(ptr) % 16; };
-  if (a.N % 8 != 0 || (a.n_split < a.N && a.n_split % 64 != 0) || (a.n_split2 < a.N && a.n_split2 % 64 != 0))
+  if (a.N % 8 != 0 || (a.mod.B > 0 && a.mod.stride % 8 != 0) || (a.n_split < a.N && a.n_split % 64 != 0) || (a.n_split2 < a.N && a.n_split2 % 64 != 0))
     return false;
   for (int i = 0; i < a.nprob; ++i) {
     const GemmProblem& p = a.p[i];
@@ -1177,68 +1182,97 @@ bool pp_layout_ok(const GemmArgs& a) {
 
 }  // namespace
 
-GemmPlan plan_gemm(const GemmArgs& a, int dtype, size_t partial_bytes, const char* family) {
+// Predicted time (us) of `units` ping-pong work units of nk k-tiles each, in
+// equal rounds of at most one unit per CU.  Measured per k-tile:
+//  - weights at hand (in a cache): the more CUs work the longer (the clock
+//    falls with the matrix load, so 168 + 168 tiles are faster than 256 + 80):
+//    256-wide 0.90 us on 84 and 120 CUs, 1.03 on 168, 1.13 on 198, 1.25 on 252;
+//    128-wide 0.58 on 96, 0.67 on 168, 0.75 on 240;
+//  - weights from HBM, where the loads in flight set the pace: 256-wide 1.28 on
+//    168 CUs, 1.40 on 252; 128-wide 0.90.
+// `cold` is the share of the tiles whose weights come from HBM: the first band
+// of rows of each problem (a model's weights exceed the caches; the later
+// bands find them).  4 us of prologue and epilogue per round, 7 per launch.
+double pp_time(int bn, int64_t units, double nk, double cold) {
+  const int64_t rounds = ceil_div64(units, kCUs);
+  const double per = double(ceil_div64(units, rounds));
+  const double warm = bn == 256 ? 0.90 + 0.35 * std::max(0.0, per - 130.0) / 122.0
+                                : 0.58 + 0.20 * std::max(0.0, per - 96.0) / 156.0;
+  const double hbm = bn == 256 ? 1.28 + 0.12 * std::max(0.0, per - 168.0) / 84.0 : 0.90;
+  return double(rounds) * (nk * (cold * hbm + (1.0 - cold) * warm) + 4.0) + 7.0;
+}
+
+// Share of the row tiles that lie in the first band of their problem.
+double first_band_share(const GemmArgs& a) {
+  int64_t first = 0, all = 0;
+  for (int i = 0; i < a.nprob; ++i) {
+    const int64_t tm = ceil_div64(a.p[i].M, kBM);
+    if (tm == 0) continue;
+    first += ceil_div64(tm, ceil_div64(tm, kBand));
+    all += tm;
+  }
+  return all > 0 ? double(first) / double(all) : 1.0;
+}
+
+GemmPlan plan_gemm(const GemmArgs& a, int dtype, size_t partial_bytes, const char* family, bool ln) {
   GemmPlan pl;
   if (dtype != AVITS_BF16) {
     pl.bn = kFB;
     pl.tiles = tiles_of(a, kFB, kFB);
     return pl;
   }
-  // Score every (column tile, K split) pair: busy fraction of the last wave
-  // of work units on the 256 CUs, times a per-tile factor (the 256-wide tile
-  // runs the ping-pong kernel and moves less L2 data per FLOP; the factors
-  // are measured on MI355X at the FLUX block shapes), times a factor for the
-  // extra fp32 partial traffic of a split.
-  const int cands[3] = {256, 192, 128};
-  const double eff[3] = {1.0, 0.74, 0.65};
   const bool wide = pp_layout_ok(a);
   const int64_t nk = a.K / kBK;
   const int64_t rows = a.p[0].M + (a.nprob > 1 ? a.p[1].M : 0);
-  double best = -1.0;
-  for (int c = 0; c < 3; ++c) {
-    const int64_t t = tiles_of(a, kBM, cands[c]);
-    if (t == 0 || (cands[c] == 256 && !wide)) continue;
-    for (int sp = 1; sp <= 4; ++sp) {
-      if (sp > 1 && (nk / sp < 4 || size_t(sp) * size_t(rows) * size_t(a.N) * sizeof(float) > partial_bytes)) break;
-      const int64_t units = t * sp;
-      const double fill = double(units) / double(ceil_div64(units, kCUs) * kCUs);
-      const double score = fill * eff[c] * (sp > 1 ? 0.95 : 1.0);
-      if (score > best + 1e-9) {
-        best = score;
-        pl.bn = cands[c];
-        pl.tiles = t;
-        pl.splits = sp;
-        pl.tail = 0;
-        pl.tail_splits = 1;
+  // The general kernel, where the ping-pong kernel's layout does not hold.
+  pl.bn = 128;
+  pl.stages = 2;
+  pl.tiles = tiles_of(a, kBM, 128);
+  if (wide && pl.tiles > 0) {
+    // The least predicted time over the column tile, the k splits of every
+    // tile and the split tail.  A split writes fp32 partials at 4.5 TB/s beside
+    // its epilogue and adds a reduce (2 us and its bytes at 4.4 TB/s); where a
+    // layer norm follows, it rides on the reduce of a fully split launch and
+    // is a launch of its own (3 us and its bytes) otherwise.
+    const double mn = double(rows) * double(a.N) * 1e-6;  // MB per byte of an output element
+    const double norm = ln ? 3.0 + 4.0 * mn / 3.5 : 0.0;
+    const double cold = first_band_share(a);
+    double best = 1e30;
+    auto consider = [&](int bn, int64_t tiles, int splits, int64_t tail, int tsp, double us) {
+      if (us >= best) return;
+      best = us;
+      pl.bn = bn;
+      pl.stages = 1;
+      pl.tiles = tiles;
+      pl.splits = splits;
+      pl.tail = tail;
+      pl.tail_splits = tsp;
+    };
+    for (int bn : {256, 128}) {
+      const int64_t t = tiles_of(a, kBM, bn);
+      consider(bn, t, 1, 0, 1, pp_time(bn, t, double(nk), cold) + norm);
+      for (int sp = 2; sp <= 4 && a.N % 8 == 0; ++sp) {
+        if (nk / sp < 4 || size_t(sp) * size_t(rows) * size_t(a.N) * sizeof(float) > partial_bytes) break;
+        const double part = 4.0 * sp * mn;
+        consider(bn, t, sp, 0, 1, pp_time(bn, t * sp, double(nk) / sp, cold) + part / 4.5 + 2.0 +
+                                      (part + (ln ? 8.0 : 6.0) * mn) / 4.4);
       }
-    }
-    // The 256-wide tile may instead split only the tiles that overrun the
-    // last full wave (the tail): the partial wave then takes 1 / tsp of a
-    // tile's time.
-    const int64_t full = t / kCUs, rem = t % kCUs;
-    if (cands[c] != 256 || full == 0 || rem == 0) continue;
-    for (int tsp = 2; tsp <= 4; ++tsp) {
-      if (rem * tsp > kCUs || nk / tsp < 4 || size_t(rem * tsp) * kBM * 256 * sizeof(float) > partial_bytes) break;
-      const double fill = double(t) / double(kCUs) / (double(full) + 1.0 / tsp);
-      const double score = fill * eff[c] * 0.95;
-      if (score > best + 1e-9) {
-        best = score;
-        pl.bn = 256;
-        pl.tiles = t;
-        pl.splits = 1;
-        pl.tail = rem;
-        pl.tail_splits = tsp;
+      // Split tail (256-wide tile): only the tiles that overrun the last full
+      // round run in k splits, in a round of their own.
+      const int64_t full = t / kCUs, rem = t % kCUs;
+      if (bn != 256 || full == 0 || rem == 0) continue;
+      for (int tsp = 2; tsp <= 4; ++tsp) {
+        const size_t bytes = size_t(rem * tsp) * kBM * 256 * sizeof(float);
+        if (rem * tsp > kCUs || nk / tsp < 4 || bytes > partial_bytes) break;
+        consider(256, t, 1, rem, tsp,
+                 pp_time(256, full * kCUs, double(nk), cold) + pp_time(256, rem * tsp, double(nk) / tsp, cold) - 7.0 +
+                     double(bytes) * 1e-6 * (1.0 / 9.0 + 1.0 / 4.4) + 2.0 + norm);
       }
     }
   }
-  pl.waves = 8;
-  // Two register stages fit the registers of the 128-wide tile only.  The staged
-  // loads are asynchronous inline assembly, so an instance that spilled a
-  // destination register would read it before the load lands: every
-  // instance must build without scratch (the build checks it).
-  pl.stages = pl.bn == 128 ? 2 : 1;
   // Tuning override "BN,SPLITS[,8[,STAGES[,TAIL,TSP]]]" (e.g. AVITS_GEMM_TILE=256,3,8,1),
-  // for one launch family with AVITS_GEMM_TILE_<family> (e.g. _gemm_o).  TAIL > 0
+  // for one launch family with AVITS_GEMM_TILE_<family> (e.g. _gemm_o): BN 256, or 128 with
+  // STAGES 1, the ping-pong kernel, anything else the general one.  TAIL > 0
   // (256-wide tile, SPLITS 1) runs the last min(TAIL, tiles) tiles in TSP k splits.
   const char* env = nullptr;
   if (family) {
@@ -1250,17 +1284,16 @@ GemmPlan plan_gemm(const GemmArgs& a, int dtype, size_t partial_bytes, const cha
   if (env) {
     int bn = 0, sp = 0, wv = 8, stg = 2, tail = 0, tsp = 1;
     const int got = sscanf(env, "%d,%d,%d,%d,%d,%d", &bn, &sp, &wv, &stg, &tail, &tsp);
-    if (bn == 256 && !wide) bn = 128;
     if (got >= 2 && (bn == 256 || bn == 192 || bn == 128) && sp >= 1 && sp <= 4 && wv == 8 &&
         (stg == 1 || stg == 2)) {
-      pl.bn = bn;
+      const bool pp = wide && (bn == 256 || (bn == 128 && stg == 1));
+      pl.bn = pp ? bn : 128;
+      pl.stages = pp ? 1 : 2;
       pl.splits = sp;
-      pl.waves = wv;
-      pl.stages = bn == 128 ? stg : 1;  // the wider tiles have one register stage only
-      pl.tiles = tiles_of(a, kBM, bn);
+      pl.tiles = tiles_of(a, kBM, pl.bn);
       pl.tail = 0;
       pl.tail_splits = 1;
-      if (got == 6 && bn == 256 && sp == 1 && tail > 0 && tsp >= 2 && tsp <= 4 && nk / tsp >= 1) {
+      if (got == 6 && pl.bn == 256 && sp == 1 && tail > 0 && tsp >= 2 && tsp <= 4 && nk / tsp >= 1) {
         pl.tail = std::min<int64_t>(tail, pl.tiles);
         pl.tail_splits = tsp;
       }
@@ -1278,11 +1311,11 @@ size_t gemm_partial_bytes(const GemmArgs& a, const GemmPlan& pl) {
 
 int launch_gemm(const GemmArgs& a, int dtype, hipStream_t s, const char* family, float* partial,
                 size_t partial_bytes, GemmPostLN* post_ln) {
-  GemmPlan pl = plan_gemm(a, dtype, partial ? partial_bytes : 0, family);
+  GemmPlan pl = plan_gemm(a, dtype, partial ? partial_bytes : 0, family, post_ln != nullptr);
   if (pl.tiles == 0) return AVITS_OK;
-  // Per-image gates are applied by the split-K reduce (the GEMM's own
-  // epilogue has one gate per launch): such a projection always runs split.
-  const bool per_image_gate = a.mod.B > 0 && a.mode0 == EPI_RESID_GATE;
+  // The general kernel's epilogue has one gate per launch: there, per-image
+  // gates are applied by the split-K reduce and such a projection runs split.
+  const bool per_image_gate = a.mod.B > 0 && a.mode0 == EPI_RESID_GATE && pl.stages == 2;
   if (per_image_gate && (pl.splits < 2 || pl.tail > 0)) {
     pl.splits = 2;
     pl.tail = 0;
@@ -1299,18 +1332,19 @@ int launch_gemm(const GemmArgs& a, int dtype, hipStream_t s, const char* family,
   if (per_image_gate && dtype != AVITS_BF16)
     return set_error(AVITS_ERR_UNSUPPORTED, "gemm %s: per-image gates need bf16", family ? family : "");
   if (dtype == AVITS_BF16) {
-    const dim3 grid(unsigned(pl.tiles * pl.splits + pl.tail * (pl.tail_splits - 1)));
     {
-    TimedLaunch timed(family, s);  // the GEMM kernel alone; the reduce is its own family
-    switch (pl.bn * 100 + pl.waves * 10 + pl.stages) {
-      case 25681:
-        hipLaunchKernelGGL(gemm_bf16_pp_kernel, grid, dim3(512), 0, s, a, partial, pl.splits, int(pl.tail),
-                           pl.tail_splits);
-        break;
-      case 19281: hipLaunchKernelGGL((gemm_bf16_kernel<192, 4, 2, 1>), grid, dim3(512), 0, s, a, partial, pl.splits); break;
-      case 12881: hipLaunchKernelGGL((gemm_bf16_kernel<128, 2, 4, 1>), grid, dim3(512), 0, s, a, partial, pl.splits); break;
-      default: hipLaunchKernelGGL((gemm_bf16_kernel<128, 2, 4, 2>), grid, dim3(512), 0, s, a, partial, pl.splits); break;
-    }
+      TimedLaunch timed(family, s);  // the GEMM kernel alone; the reduce is its own family
+      const int64_t units = pl.tiles * pl.splits + pl.tail * (pl.tail_splits - 1);
+      // Ping-pong kernel: equal rounds (a split tail: full rounds, then its own).
+      const int64_t rounds = ceil_div64(units, kCUs);
+      const dim3 pgrid(unsigned(pl.tail > 0 ? std::min<int64_t>(units, kCUs) : ceil_div64(units, rounds)));
+      if (pl.stages == 2)
+        hipLaunchKernelGGL(gemm_bf16_kernel, dim3(unsigned(units)), dim3(512), 0, s, a, partial, pl.splits);
+      else if (pl.bn == 256)
+        hipLaunchKernelGGL(gemm_bf16_pp_kernel<256>, pgrid, dim3(512), 0, s, a, partial, int(units), pl.splits,
+                           int(pl.tail), pl.tail_splits);
+      else
+        hipLaunchKernelGGL(gemm_bf16_pp_kernel<128>, pgrid, dim3(512), 0, s, a, partial, int(units), pl.splits, 0, 1);
     }
     if (post_ln) post_ln->done = false;
     if (pl.tail > 0) {

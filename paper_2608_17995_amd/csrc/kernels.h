@@ -78,21 +78,22 @@ struct GemmArgs {
   int64_t n_split, n_split2;  // region starts; >= N when unused
   int mode0, mode1, mode2;
   // Per-image gates (EPI_RESID_GATE) and post-LN modulation: row m of
-  // problem p takes gate + mod_offset(mod, p.row0 + m).  Applied by the
-  // split-K reduce kernels, so launch_gemm runs such a projection split.
+  // problem p takes gate + mod_offset(mod, p.row0 + m) (in the ping-pong
+  // kernel's epilogue or a split-K reduce; launch_gemm runs the general
+  // kernel split for it).
   ModRows mod;
 };
 
 struct GemmPlan {
   int bn = 0;          // column tile
   int splits = 1;      // K splits (fp32 partials + reduce when > 1)
-  int waves = 8;       // waves per workgroup
-  int stages = 2;      // register staging depth of the k-tile pipeline (1 or 2)
+  int stages = 1;      // 1: the ping-pong kernel; 2: the general kernel
   int64_t tiles = 0;   // output tiles
   int64_t tail = 0;    // last tiles run in tail_splits k splits (256-wide tile, splits == 1)
   int tail_splits = 1;
 };
-GemmPlan plan_gemm(const GemmArgs& a, int dtype, size_t partial_bytes, const char* family = nullptr);
+// ln: a layer norm of the output rows follows (GemmPostLN below).
+GemmPlan plan_gemm(const GemmArgs& a, int dtype, size_t partial_bytes, const char* family = nullptr, bool ln = false);
 size_t gemm_partial_bytes(const GemmArgs& a, const GemmPlan& pl);
 // `partial` is scratch for split-K partial sums; when it is null or smaller
 // than the plan needs, the GEMM runs unsplit.

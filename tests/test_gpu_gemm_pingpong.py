@@ -1,12 +1,13 @@
-"""The 256-wide ping-pong GEMM at the edges of its ring of LDS tiles (one to
-five 64-wide k-tiles: fewer tiles than W slots, and the first wraps of both
-rings), of its 128 x 64 wave blocks (rows and columns that end inside one, at
-one, and one past one) and of its bands of row tiles (one band, two equal
-ones, three of unequal size), element by element within the rounding bound of
-the other tile forms; the same kernel through a whole block with an odd text
-length (a transposed store that starts at an odd element) unsplit, in two and
-three k splits and with a split tail; and operands off the 16-byte grid, which
-another kernel takes."""
+"""The ping-pong GEMM (256- and 128-wide) at the edges of its rings of LDS tiles
+(one to five 64-wide k-tiles: fewer tiles than slots, and the first wraps of
+both rings), of its wave blocks (rows and columns that end inside one, at
+one, and one past one), of its bands of row tiles (one band, two equal ones,
+three of unequal size) and of its rounds (more tiles than CUs: the last round
+full or not), element by element within the rounding bound of the other tile
+forms; the same kernel through a whole block with an odd text length (a
+transposed store that starts at an odd element) unsplit, in two and three k
+splits and with a split tail; and operands off the 16-byte grid, which another
+kernel takes."""
 import numpy as np
 import pytest
 import torch
@@ -21,16 +22,17 @@ from synth import generator as G
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(127, 72, 64), (128, 64, 128), (129, 200, 192), (256, 256, 256), (391, 328, 320),
-          (2307, 136, 64), (4096, 72, 64), (4400, 264, 128)]
+          (2307, 136, 64), (4096, 72, 64), (4400, 264, 128), (4100, 3976, 64)]
 
 
+@pytest.mark.parametrize("plan", ["256,1", "128,1,8,1"])
 @pytest.mark.parametrize("M,N,K", SHAPES, ids=[f"{m}x{n}x{k}" for m, n, k in SHAPES])
-def test_linear_edges(gpu, monkeypatch, M, N, K):
-    got, ref, mag, tail = _run(gpu, monkeypatch, M, N, K, torch.bfloat16, "256,1")
+def test_linear_edges(gpu, monkeypatch, plan, M, N, K):
+    got, ref, mag, tail = _run(gpu, monkeypatch, M, N, K, torch.bfloat16, plan)
     _check(got, ref, mag, tail, 2.0 ** -8, K)
 
 
-@pytest.mark.parametrize("plan", ["256,1", "256,2", "256,3", "256,1,8,1,2,2"])
+@pytest.mark.parametrize("plan", ["256,1", "256,2", "256,3", "256,1,8,1,2,2", "128,1,8,1", "128,3,8,1"])
 @pytest.mark.parametrize("kind", ["double", "single"])
 def test_block_odd_rows(gpu, monkeypatch, kind, plan):
     monkeypatch.setenv("AVITS_GEMM_TILE", plan)
