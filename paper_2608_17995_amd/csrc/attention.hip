@@ -29,7 +29,7 @@
 // splits the overrun units (or, for small grids, every unit) along the keys:
 // each piece writes its unnormalised output and (max, sum) per row, and a
 // combine kernel merges the pieces in key order.
-// fp32: one thread per query row on the VALU (exactness path).
+// fp32: attn_f32_kernel (the exactness path).
 #include <stdio.h>
 #include <stdlib.h>
 
@@ -553,72 +553,121 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const AttnArgs a) {
   }
 }
 
-// fp32 VALU attention: one thread per query row, 32-key tiles in LDS.
-constexpr int kFRows = 64, kFKT = 32;
+// fp32 attention on v_mfma_f32_16x16x4_f32: a workgroup of eight waves owns 16
+// query rows of one head, wave w the 16-key tiles w, w + 8, ...; each wave
+// keeps its own online softmax, and the eight results meet in LDS, in wave
+// order.  As in the bf16 kernel the products are transposed (S^T = K Q^T,
+// O^T = V^T P^T): register r of a lane (g = lane / 16) is key 4 g + r of query
+// lane % 16, so the probabilities are the second product's operand as they
+// stand, and its V^T operand is one 16-byte load.
+// Bound by: latency at the sizes in use.  One thread per query row with the
+// keys in a serial loop, which this replaces, put 20 waves on the chip at 288
+// rows and 4 heads and took 214 us.
+constexpr int kFRows = 16, kFWaves = 8;
 template <int DH, bool WITH_V>
-__global__ __launch_bounds__(kFRows) void attn_f32_kernel(const AttnArgs a) {
-  __shared__ float Ks[kFKT * DH];
-  __shared__ float Vs[WITH_V ? kFKT * DH : 1];
-  const int h = blockIdx.y;
-  const int64_t row = int64_t(blockIdx.x) * kFRows + threadIdx.x;
-  const bool ok = row < a.Sq;
-  const float* Q = static_cast<const float*>(a.q);
-  const float* K = static_cast<const float*>(a.k);
-  const float* VT = static_cast<const float*>(a.vt);
-  float q[DH], o[WITH_V ? DH : 1];
+__global__ __launch_bounds__(64 * kFWaves) void attn_f32_kernel(const AttnArgs a) {
+  constexpr int kC = DH / 16, kP = DH + 4;
+  __shared__ __attribute__((aligned(16))) float so[WITH_V ? kFWaves * kFRows * kP : 4];
+  __shared__ float4 sml[kFWaves][kFRows];  // max, sum, sum over the keys < mass_keys
+  const int h = blockIdx.y, tid = threadIdx.x, lane = tid % kWave, l16 = lane % 16, g = lane / 16;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int64_t q0 = int64_t(blockIdx.x) * kFRows;
+  const float* K = static_cast<const float*>(a.k) + h * a.k_head + 4 * g;
+  const float* VT = static_cast<const float*>(a.vt) + (int64_t(h) * DH + l16) * a.ldvt + 4 * g;
+  f32x4 qf[kC], kf[kC], vf[kC], o[kC];
+  {
+    const float* Q = static_cast<const float*>(a.q) + std::min<int64_t>(q0 + l16, a.Sq - 1) * a.q_tok + h * a.q_head + 4 * g;
 #pragma unroll
-  for (int c = 0; c < DH; ++c) q[c] = ok ? Q[row * a.q_tok + h * a.q_head + c] : 0.f;
-#pragma unroll
-  for (int c = 0; c < (WITH_V ? DH : 1); ++c) o[c] = 0.f;
+    for (int j = 0; j < kC; ++j) {
+      qf[j] = load4u(Q + 16 * j);
+      o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  }
   const float scale = rsqrtf(float(DH));
-  float m = -INFINITY, l = 0.f, tl = 0.f;  // tl: the part of l from keys < a.mass_keys
-  for (int64_t k0 = 0; k0 < a.Sk; k0 += kFKT) {
-    __syncthreads();
-    for (int p = threadIdx.x; p < kFKT * DH; p += kFRows) {
-      const int key = p / DH, c = p % DH;
-      const bool kv = k0 + key < a.Sk;
-      Ks[p] = kv ? K[(k0 + key) * a.k_tok + h * a.k_head + c] : 0.f;
-      if constexpr (WITH_V) Vs[p] = kv ? VT[(int64_t(h) * DH + c) * a.ldvt + k0 + key] : 0.f;
-    }
-    __syncthreads();
-    const int nk = int(std::min<int64_t>(kFKT, a.Sk - k0));
-    float s[kFKT];
-    float mx = m;
-    for (int j = 0; j < kFKT; ++j) {
-      float acc = 0.f;
+  float m = -INFINITY, l = 0.f, tl = 0.f;
+  const int64_t n_t = (a.Sk + 15) / 16;
+  // Rows past the last key repeat it; their logits are -inf.
+  auto load_k = [&](int64_t t) {
+    const float* src = K + std::min<int64_t>(16 * t + l16, a.Sk - 1) * a.k_tok;
 #pragma unroll
-      for (int c = 0; c < DH; ++c) acc = fmaf(q[c], Ks[j * DH + c], acc);
-      s[j] = j < nk ? acc * scale : -INFINITY;
-      mx = fmaxf(mx, s[j]);
+    for (int j = 0; j < kC; ++j) kf[j] = load4u(src + 16 * j);
+  };
+  load_k(wave);
+  for (int64_t t = wave; t < n_t; t += kFWaves) {
+    if constexpr (WITH_V) {  // the padding of a V^T row is readable but may hold anything
+#pragma unroll
+      for (int j = 0; j < kC; ++j) vf[j] = load4u(VT + int64_t(16 * j) * a.ldvt + 16 * t);
     }
-    const float corr = expf(m - mx);
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < kC; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = mfma16x16x4(kf[j][e], qf[j][e], s);
+    load_k(t + kFWaves);
+    const int64_t key = 16 * t + 4 * g;
+    float mx = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      s[r] = key + r < a.Sk ? s[r] * scale : -INFINITY;
+      mx = fmaxf(mx, s[r]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(m, max_xor32(mx));
+    const float ref = mx == -INFINITY ? 0.f : mx;  // only -inf so far: every exponential is 0
+    const float corr = expf(m - ref);
     m = mx;
     l *= corr;
     tl *= corr;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      s[r] = expf(s[r] - ref);
+      l += s[r];
+      tl += key + r < a.mass_keys ? s[r] : 0.f;
+    }
     if constexpr (WITH_V) {
 #pragma unroll
-      for (int c = 0; c < DH; ++c) o[c] *= corr;
-    }
-    for (int j = 0; j < nk; ++j) {
-      const float e = expf(s[j] - m);
-      l += e;
-      tl += k0 + j < a.mass_keys ? e : 0.f;
-      if constexpr (WITH_V) {
+      for (int j = 0; j < kC; ++j) {
+        o[j] *= corr;
 #pragma unroll
-        for (int c = 0; c < DH; ++c) o[c] = fmaf(e, Vs[j * DH + c], o[c]);
+        for (int r = 0; r < 4; ++r) o[j] = mfma16x16x4(key + r < a.Sk ? vf[j][r] : 0.f, s[r], o[j]);
       }
     }
   }
-  if (!ok) return;
-  if (a.lse) a.lse[int64_t(h) * a.Sq + row] = m + logf(l);
+  l += __shfl_xor(l, 16);
+  l = sum_xor32(l);
+  tl += __shfl_xor(tl, 16);
+  tl = sum_xor32(tl);
+  if (g == 0) sml[wave][l16] = make_float4(m, l, tl, 0.f);
+  if constexpr (WITH_V) {
+#pragma unroll
+    for (int j = 0; j < kC; ++j) *reinterpret_cast<f32x4*>(&so[(wave * kFRows + l16) * kP + 16 * j + 4 * g]) = o[j];
+  }
+  __syncthreads();
+  constexpr int kQuads = WITH_V ? DH / 4 : 1;  // groups of four output columns
+  if (tid >= kFRows * kQuads) return;
+  const int r = tid / kQuads, c = tid % kQuads;
+  const int64_t row = q0 + r;
+  if (row >= a.Sq) return;
+  float mt = -INFINITY, den = 0.f, tden = 0.f;
+#pragma unroll
+  for (int w = 0; w < kFWaves; ++w) mt = fmaxf(mt, sml[w][r].x);
+  const float ref = mt == -INFINITY ? 0.f : mt;
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < kFWaves; ++w) {
+    const float4 ml = sml[w][r];
+    const float wgt = expf(ml.x - ref);
+    den = fmaf(wgt, ml.y, den);
+    tden = fmaf(wgt, ml.z, tden);
+    if constexpr (WITH_V) v += *reinterpret_cast<const f32x4*>(&so[(w * kFRows + r) * kP + 4 * c]) * wgt;
+  }
+  if constexpr (WITH_V)
+    *reinterpret_cast<f32x4u*>(static_cast<float*>(a.o) + row * a.ldo + int64_t(h) * DH + 4 * c) = v / den;
+  if (c != 0) return;
+  if (a.lse) a.lse[int64_t(h) * a.Sq + row] = mt + logf(den);
   if (a.mass) {
     float* dst = a.mass + int64_t(h) * a.Sq + row;
-    *dst = (a.mass_accumulate ? *dst : 0.f) + tl / l;
-  }
-  if constexpr (WITH_V) {
-    float* dst = static_cast<float*>(a.o) + row * a.ldo + int64_t(h) * DH;
-#pragma unroll
-    for (int c = 0; c < DH; ++c) dst[c] = o[c] / l;
+    *dst = (a.mass_accumulate ? *dst : 0.f) + tden / den;
   }
 }
 
@@ -773,8 +822,8 @@ void launch_dh(AttnArgs a, int dtype, hipStream_t s) {
     }
   } else {
     const dim3 grid(unsigned(ceil_div64(a.Sq, kFRows)), unsigned(a.H));
-    if (with_v) hipLaunchKernelGGL((attn_f32_kernel<DH, true>), grid, dim3(kFRows), 0, s, a);
-    else hipLaunchKernelGGL((attn_f32_kernel<DH, false>), grid, dim3(kFRows), 0, s, a);
+    if (with_v) hipLaunchKernelGGL((attn_f32_kernel<DH, true>), grid, dim3(64 * kFWaves), 0, s, a);
+    else hipLaunchKernelGGL((attn_f32_kernel<DH, false>), grid, dim3(64 * kFWaves), 0, s, a);
   }
 }
 

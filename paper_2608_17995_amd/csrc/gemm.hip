@@ -28,7 +28,8 @@
 //    split tail): they run after the whole tiles, in 2-4 k splits, and a
 //    small reduce sums their partials, so the partial wave takes a fraction
 //    of a tile's time instead of a whole one.
-// fp32 path: 64x64 tiles on the VALU (the exactness path).
+// fp32 path (the exactness path): gemm_f32_kernel on the fp32 matrix instructions, and for many tiles
+// gemm_f32_valu_kernel.
 #include <stdio.h>
 #include <stdlib.h>
 
@@ -1111,9 +1112,80 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmArgs a, co
   epilogue8(a, p, m, n, v);
 }
 
-// fp32 VALU GEMM: 64x64 tile, 16x16 threads, 4x4 outputs per thread.
-constexpr int kFB = 64, kFK = 16;
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmArgs a) {
+// fp32 GEMM of few tiles, on v_mfma_f32_32x32x2_f32: the eight waves of a
+// workgroup share the contraction of one 32 x 32 tile, in steps of 16 (wave w
+// takes steps w, w + 8, ...); their sums meet in LDS in wave order.  Operands
+// go from the caches to registers: a lane holds eight consecutive k of one row
+// of each, and the same k of both halves of the wave feed one product (any
+// order of the contraction is as good).
+// Bound by: latency.  The fp32 block of 288 rows and width 256 has 20 to 80
+// tiles of 64 x 64, each a serial loop over K on one CU of 256; tiles of 32 x 32
+// with K over eight waves take four times the CUs and an eighth of the chain.
+// Measured against the 64 x 64 kernel: 288 x 768 x 256 18.9 -> 9.4 us, 288 x 256 x
+// 1024 58.7 -> 12.8, 1024 x 384 x 1536 98 -> 30; error against 64 bits (relative,
+// 2-norm) 2.9e-7 -> 1.2e-7 at K = 256, 5.7e-7 -> 2.1e-7 at 1024.
+constexpr int kFT = 32, kFK = 16, kFWaves = 8;
+__global__ __launch_bounds__(64 * kFWaves) void gemm_f32_kernel(const GemmArgs a) {
+  constexpr int kP = kFT + 4, U = 2;
+  __shared__ __attribute__((aligned(16))) float red[kFWaves][kFT * kP];
+  int prob, ks;
+  int64_t m0, n0;
+  if (!map_tile(a, kFT, kFT, 1, prob, m0, n0, ks)) return;
+  const GemmProblem p = prob ? a.p[1] : a.p[0];  // by value: a select, no indexed copy of the arguments
+  const int tid = threadIdx.x, lane = tid % kWave, l32 = lane % 32, hi = lane / 32;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  // Rows past the end repeat the last one; their results are not stored.
+  const float* A = static_cast<const float*>(p.A) + std::min<int64_t>(m0 + l32, p.M - 1) * p.lda + 8 * hi;
+  const float* W = static_cast<const float*>(p.W) + std::min<int64_t>(n0 + l32, a.N - 1) * a.K + 8 * hi;
+  struct Step {
+    f32x4 a[2], w[2];
+  };
+  const int nk = int(a.K / kFK);
+  auto load = [&](Step (&st)[U], int s) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t k = int64_t(std::min(s + kFWaves * u, nk - 1)) * kFK;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        st[u].a[e] = load4u(A + k + 4 * e);
+        st[u].w[e] = load4u(W + k + 4 * e);
+      }
+    }
+  };
+  f32x16 acc = {};
+  Step cur[U], nxt[U];
+  load(cur, wave);
+  for (int s = wave; s < nk; s += kFWaves * U) {
+    load(nxt, s + kFWaves * U);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (s + kFWaves * u < nk) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(cur[u].w[e / 4][e % 4], cur[u].a[e / 4][e % 4], acc, 0, 0, 0);
+      }
+      cur[u] = nxt[u];
+    }
+  }
+  // acc[4 q + r] = C[row l32][column 8 q + 4 hi + r] of the tile.
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    *reinterpret_cast<f32x4*>(&red[wave][l32 * kP + 8 * q + 4 * hi]) =
+        f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+  __syncthreads();
+  if (tid >= kFT * kFT / 4) return;
+  const int r = tid / 8, c = tid % 8 * 4;
+  f32x4 v = *reinterpret_cast<const f32x4*>(&red[0][r * kP + c]);
+#pragma unroll
+  for (int w = 1; w < kFWaves; ++w) v += *reinterpret_cast<const f32x4*>(&red[w][r * kP + c]);
+  const int64_t m = m0 + r, n = n0 + c;
+  if (m < p.M && n < a.N) epilogue4<float>(a, p, m, n, v[0], v[1], v[2], v[3]);
+}
+
+
+// fp32 GEMM of at least one 64 x 64 tile per CU, on the VALU: 64x64 tile, 16x16 threads, 4x4 outputs per thread.
+constexpr int kFB = 64;
+__global__ __launch_bounds__(256) void gemm_f32_valu_kernel(const GemmArgs a) {
   __shared__ float As[kFK][kFB + 4];
   __shared__ float Ws[kFK][kFB + 4];
   int prob, ks;
@@ -1217,8 +1289,11 @@ double first_band_share(const GemmArgs& a) {
 GemmPlan plan_gemm(const GemmArgs& a, int dtype, size_t partial_bytes, const char* family, bool ln) {
   GemmPlan pl;
   if (dtype != AVITS_BF16) {
-    pl.bn = kFB;
-    pl.tiles = tiles_of(a, kFB, kFB);
+    // fp32: 64 x 64 tiles on the VALU where every CU gets one, else 32 x 32 with
+    // the contraction over eight waves.  Measured, 64 against 32: 384 tiles of
+    // 64 x 64 with K = 384 32.5 against 37.9 us, 96 tiles with K = 1536 98 against 30.
+    pl.bn = tiles_of(a, kFB, kFB) >= kCUs ? kFB : kFT;
+    pl.tiles = tiles_of(a, pl.bn, pl.bn);
     return pl;
   }
   const bool wide = pp_layout_ok(a);
@@ -1370,7 +1445,8 @@ int launch_gemm(const GemmArgs& a, int dtype, hipStream_t s, const char* family,
     }
   } else {
     TimedLaunch timed(family, s);
-    hipLaunchKernelGGL(gemm_f32_kernel, dim3(unsigned(pl.tiles)), dim3(256), 0, s, a);
+    if (pl.bn == kFB) hipLaunchKernelGGL(gemm_f32_valu_kernel, dim3(unsigned(pl.tiles)), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(gemm_f32_kernel, dim3(unsigned(pl.tiles)), dim3(64 * kFWaves), 0, s, a);
   }
   return launch_status("gemm");
 }

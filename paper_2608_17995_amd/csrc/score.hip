@@ -292,15 +292,20 @@ __global__ __launch_bounds__(64) void combine_kernel(const float* __restrict__ p
   if (threadIdx.x == 0) mm[blockIdx.x] = make_float4(amin, amax, vmin, vmax);
 }
 
-// 1'. spatial partials, fp32 on the VALU: one thread per image row.
+// 1'. spatial partials, fp32: a wave per 16 image rows of one head, the text
+// keys 16 at a time on v_mfma_f32_16x16x4_f32 (S^T = K Q^T: register r of a
+// lane is key 4 (lane / 16) + r of image row lane % 16).  Bound by latency: one
+// thread per image row with a serial loop over the keys, which this replaces,
+// took 25 us for 1024 rows, 32 keys and 4 heads of 64.
+constexpr int kSpF32Rows = 64;  // image rows per workgroup
 template <int DH>
-__global__ __launch_bounds__(128) void spatial_f32_kernel(const float* __restrict__ q,
+__global__ __launch_bounds__(256) void spatial_f32_kernel(const float* __restrict__ q,
                                                           const float* __restrict__ ktxt,
                                                           const float* __restrict__ lse, int N, int L, int H,
                                                           float* __restrict__ part) {
-  __shared__ float ks[kSpKeys * DH];
-  const int h = blockIdx.y;
-  const int row = blockIdx.x * 128 + threadIdx.x;
+  constexpr int kC = DH / 16;
+  const int h = blockIdx.y, lane = threadIdx.x % kWave, l16 = lane % 16, g = lane / 16;
+  const int row = blockIdx.x * kSpF32Rows + threadIdx.x / kWave * 16 + l16, rc = min(row, N - 1);
   {  // image blockIdx.z
     const int64_t img = blockIdx.z;
     q += img * N * H * DH;
@@ -308,29 +313,37 @@ __global__ __launch_bounds__(128) void spatial_f32_kernel(const float* __restric
     lse += img * H * N;
     part += img * H * N;
   }
-  const bool ok = row < N;
-  float qr[DH];
+  f32x4 qf[kC], kf[kC];
 #pragma unroll
-  for (int c = 0; c < DH; ++c) qr[c] = ok ? q[(int64_t(row) * H + h) * DH + c] : 0.f;
-  const float l = ok ? lse[int64_t(h) * N + row] : 0.f;
-  const float scale = rsqrtf(float(DH));
-  float acc = 0.f;
-  for (int k0 = 0; k0 < L; k0 += kSpKeys) {
-    __syncthreads();
-    for (int p = threadIdx.x; p < kSpKeys * DH; p += 128) {
-      const int key = p / DH, c = p % DH;
-      ks[p] = k0 + key < L ? ktxt[(int64_t(k0 + key) * H + h) * DH + c] : 0.f;
-    }
-    __syncthreads();
-    const int nk = min(kSpKeys, L - k0);
-    for (int j = 0; j < nk; ++j) {
-      float s = 0.f;
+  for (int j = 0; j < kC; ++j) qf[j] = load4u(q + (int64_t(rc) * H + h) * DH + 16 * j + 4 * g);
+  const float l = lse[int64_t(h) * N + rc], scale = rsqrtf(float(DH));
+  // Keys past the last repeat it and are not counted.
+  auto load_k = [&](int k0) {
 #pragma unroll
-      for (int c = 0; c < DH; ++c) s = fmaf(qr[c], ks[j * DH + c], s);
-      acc += expf(s * scale - l);
+    for (int j = 0; j < kC; ++j) kf[j] = load4u(ktxt + (int64_t(min(k0 + l16, L - 1)) * H + h) * DH + 16 * j + 4 * g);
+  };
+  double acc = 0.0;  // the min-max normalisation magnifies what the extreme rows lose
+  load_k(0);
+  for (int k0 = 0; k0 < L; k0 += 16) {
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < kC; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = mfma16x16x4(kf[j][e], qf[j][e], s);
+    if (k0 + 16 < L) load_k(k0 + 16);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      // exp(x - l), with what the difference loses to rounding (up to 5e-7 at the
+      // usual l of 8 to 16, times e) put back.
+      const float x = s[r] * scale, t = x - l, back = t - x;
+      const float lost = (x - (t - back)) - (l + back);
+      const float e = expf(t);
+      acc += k0 + 4 * g + r < L ? double(fabsf(t) < INFINITY ? fmaf(e, lost, e) : e) : 0.0;
     }
   }
-  if (ok) part[int64_t(h) * N + row] = acc;
+  acc += __shfl_xor(acc, 16);
+  acc += __shfl_xor(acc, 32);
+  if (row < N && g == 0) part[int64_t(h) * N + row] = float(acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -656,12 +669,12 @@ int score_launch(const char* who, const void* latent_q, const void* text_k, cons
   } else {
     {
       TimedLaunch timed("score_spatial", s);
-      const dim3 grid(unsigned((N + 127) / 128), unsigned(H), nimg);
+      const dim3 grid(unsigned((N + kSpF32Rows - 1) / kSpF32Rows), unsigned(H), nimg);
       if (d == 128)
-        hipLaunchKernelGGL(spatial_f32_kernel<128>, grid, dim3(128), 0, s, (const float*)latent_q,
+        hipLaunchKernelGGL(spatial_f32_kernel<128>, grid, dim3(256), 0, s, (const float*)latent_q,
                            (const float*)text_k, row_lse, n, l, H, ws.part);
       else
-        hipLaunchKernelGGL(spatial_f32_kernel<64>, grid, dim3(128), 0, s, (const float*)latent_q,
+        hipLaunchKernelGGL(spatial_f32_kernel<64>, grid, dim3(256), 0, s, (const float*)latent_q,
                            (const float*)text_k, row_lse, n, l, H, ws.part);
     }
     nmm = int(std::min<int64_t>(kTmpBlocks, (N + 3) / 4));
