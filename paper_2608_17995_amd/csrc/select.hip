@@ -14,6 +14,7 @@
 // cost is latency, not bandwidth, and the keys stay in registers between
 // passes (each thread holds consecutive elements, so the emission is one
 // workgroup scan).  Larger N runs the same passes grid-wide (below).
+#include <algorithm>
 #include <mutex>
 
 #include "common.h"
@@ -51,32 +52,74 @@ __global__ __launch_bounds__(kThreads) void radix_select_batched_kernel(const fl
 // ---------------------------------------------------------------------------
 // Grid-wide radix select for N above what one workgroup holds in registers:
 // the same four digit passes and index-order emission, spread over the GPU.
-//   init            state: prefix 0, need k, histograms zeroed
-//   4 x hist, scan  every workgroup histograms the current digit of the keys
-//                   that match the prefix (LDS, then one atomic per bin: the
-//                   sums are order-free); one workgroup picks the digit
-//   count           per 4096-element chunk: keys > T and keys == T
-//   offsets         one workgroup scans the chunk counts in index order:
-//                   each chunk's output offset and its quota of keys == T
-//   emit            each chunk writes its selected indices in index order
+//   init     histograms zeroed, need k
+//   4 x hist every workgroup first picks the last pass's digit from its global
+//            histogram, then histograms this pass's digit of the keys that match
+//            the prefix (LDS, then one atomic per bin: the sums are order-free)
+//   count    per chunk of 4096: keys > T and keys == T
+//   emit     each chunk writes its selected indices in index order, after
+//            summing the counts of the chunks before it
+// Past kSumChunks chunks, where those sums (which grow with the square of N)
+// cost as much as a launch, one workgroup scans the counts between the two
+// (offsets).  Bound by: launches, up to a few million scores (2^20: 4 MB, under
+// 1 us of memory time): seven, where a launch per digit pick and the offset scan
+// made twelve: N = 2^18 49 -> 38 us, 2^20 54 -> 40, 2^23 115 -> 77, 2^25 252 -> 244.
+// Loads issued four deep in the histogram passes change nothing.
 // Scores are read with 16-byte loads; every pass streams them once.
 constexpr int kGT = 256;               // threads per workgroup of the grid passes
 constexpr int kGWaves = kGT / kWave;
-constexpr int kHistBlocks = 2048;      // histogram workgroups (grid-stride)
+constexpr int kHT = 1024;              // threads per histogram workgroup
+constexpr int kHWaves = kHT / kWave;
+// Histogram workgroups at most (grid-stride), and keys for each.  Each ends
+// with an atomic per bin, on bins that all share: many small workgroups spend
+// their time there (256 of 256 threads on 2^20 scores: 9 us a pass).
+constexpr int kHistBlocks = 256, kHistKeys = 16 * kHT;
 constexpr int kChunk = 16 * kGT;       // elements per count / emit workgroup (16 per thread)
+constexpr int kSumChunks = 2048;       // chunks whose counts the emission sums itself
 
 struct SelState {
-  uint32_t prefix;                     // digits chosen so far, in place
-  uint32_t need;                       // rank of the k-th largest among keys matching the prefix
-  uint32_t pad[62];
+  // Before pass p (4: after the last): the digits chosen so far, in place, and
+  // the rank of the k-th largest among the keys matching them.
+  uint32_t prefix[5], need[5];
+  uint32_t pad[54];
   uint32_t hist[4][256];               // global digit histograms, one per pass
 };
 
 __global__ __launch_bounds__(kGT) void select_init_kernel(SelState* __restrict__ st, uint32_t k) {
   for (int b = threadIdx.x; b < 4 * 256; b += kGT) (&st->hist[0][0])[b] = 0u;
   if (threadIdx.x == 0) {
-    st->prefix = 0u;
-    st->need = k;
+    st->prefix[0] = 0u;
+    st->need[0] = k;
+  }
+}
+
+// State before pass `pass`, by every workgroup of a launch (the first one
+// records it): the digit b of the pass before with (matching keys above b) <
+// need <= (matching keys at or above b).
+__device__ __forceinline__ void select_pick(SelState* __restrict__ st, int pass, uint32_t& prefix, uint32_t& need) {
+  __shared__ uint32_t wsum[kGWaves], picked[2];
+  if (pass == 0) {
+    prefix = st->prefix[0];
+    need = st->need[0];
+    return;
+  }
+  const int b = threadIdx.x, wave = b / kWave, lane = b % kWave;
+  const uint32_t c = b < 256 ? st->hist[pass - 1][b] : 0u, last = st->prefix[pass - 1], rank = st->need[pass - 1];
+  const uint32_t suf = wave_incl_suffix_u32(c);  // suffix sum inside the wave, high lanes down
+  if (lane == 0 && b < 256) wsum[wave] = suf;
+  __syncthreads();
+  uint32_t above = suf - c;
+  for (int w = wave + 1; w < kGWaves; ++w) above += wsum[w];
+  if (b < 256 && above < rank && above + c >= rank) {
+    picked[0] = last | uint32_t(b) << (32 - 8 * pass);
+    picked[1] = rank - above;
+  }
+  __syncthreads();
+  prefix = picked[0];
+  need = picked[1];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->prefix[pass] = prefix;
+    st->need[pass] = need;
   }
 }
 
@@ -101,19 +144,20 @@ __device__ __forceinline__ void load_keys4(const float* __restrict__ scores, con
   }
 }
 
-constexpr int kSubHist = 4;  // LDS histogram copies per wave (lane % 4): spreads atomics on one bin
+constexpr int kSubHist = 2;  // LDS histogram copies per wave (lane % 2): spreads atomics on one bin
 
-__global__ __launch_bounds__(kGT) void select_hist_kernel(const float* __restrict__ scores,
-    const float* __restrict__ delta, int64_t N, int pass,
+__global__ __launch_bounds__(kHT) void select_hist_kernel(const float* __restrict__ scores,
+                                                          const float* __restrict__ delta, int64_t N, int pass,
                                                           SelState* __restrict__ st) {
-  __shared__ uint32_t hs[kGWaves * kSubHist][256];
+  __shared__ uint32_t hs[kHWaves * kSubHist][256];
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
   uint32_t* h = hs[wave * kSubHist + (lane & (kSubHist - 1))];
-  for (int b = tid; b < kGWaves * kSubHist * 256; b += kGT) (&hs[0][0])[b] = 0u;
+  for (int b = tid; b < kHWaves * kSubHist * 256; b += kHT) (&hs[0][0])[b] = 0u;
+  uint32_t prefix, need;
+  select_pick(st, pass, prefix, need);
   __syncthreads();
   const int shift = 24 - 8 * pass;
   const uint32_t mask = pass ? 0xffffffffu << (32 - 8 * pass) : 0u;
-  const uint32_t prefix = st->prefix & mask;
   // The top digit of similar scores coincides (one exponent covers most of a
   // min-max-normalised score range), so in the first pass a wave adds its two
   // most frequent-looking digits with one atomic each (ballot) before the
@@ -151,7 +195,7 @@ __global__ __launch_bounds__(kGT) void select_hist_kernel(const float* __restric
   // Grid-stride over groups of four keys, the next group's 16-byte loads in
   // flight while the current group is counted (groups that are not whole
   // or not 16-byte aligned take load_keys4's element path instead).
-  const int64_t groups = (N + 3) / 4, stride = int64_t(gridDim.x) * kGT;
+  const int64_t groups = (N + 3) / 4, stride = int64_t(gridDim.x) * kHT;
   const bool al = (reinterpret_cast<uintptr_t>(scores) & 15) == 0 &&
                   (!delta || (reinterpret_cast<uintptr_t>(delta) & 15) == 0);
   float4 rv = make_float4(0.f, 0.f, 0.f, 0.f), rd = rv;
@@ -161,7 +205,7 @@ __global__ __launch_bounds__(kGT) void select_hist_kernel(const float* __restric
       if (delta) rd = *reinterpret_cast<const float4*>(delta + i0);
     }
   };
-  int64_t g = int64_t(blockIdx.x) * kGT + tid;
+  int64_t g = int64_t(blockIdx.x) * kHT + tid;
   issue(4 * g);
   for (; g - tid < groups; g += stride) {
     uint32_t key[4];
@@ -181,31 +225,17 @@ __global__ __launch_bounds__(kGT) void select_hist_kernel(const float* __restric
     count4(key, live);
   }
   __syncthreads();
-  for (int b = tid; b < 256; b += kGT) {
-    uint32_t c = 0u;
+  // Four threads per bin, a quarter of the copies each.
+  constexpr int kPer = kHWaves * kSubHist / 4;
+  const int b = tid % 256, quarter = tid / 256;
+  uint32_t c = 0u;
 #pragma unroll
-    for (int w = 0; w < kGWaves * kSubHist; ++w) c += hs[w][b];
-    if (c) atomicAdd(&st->hist[pass][b], c);
-  }
-}
-
-// One workgroup: the digit b of this pass with (matching keys above b) <
-// need <= (matching keys at or above b).
-__global__ __launch_bounds__(256) void select_scan_kernel(int pass, SelState* __restrict__ st) {
-  __shared__ uint32_t wsum[4];
-  const int b = threadIdx.x, wave = b / kWave, lane = b % kWave;
-  const uint32_t c = st->hist[pass][b];
-  const uint32_t suf = wave_incl_suffix_u32(c);  // suffix sum inside the wave, high lanes down
-  if (lane == 0) wsum[wave] = suf;
+  for (int w = 0; w < kPer; ++w) c += hs[quarter * kPer + w][b];
+  hs[quarter * kPer][b] = c;  // read by this thread alone until the barrier
   __syncthreads();
-  uint32_t higher = 0u;
-  for (int w = wave + 1; w < 4; ++w) higher += wsum[w];
-  const uint32_t above = suf - c + higher, need = st->need;
-  __syncthreads();
-  if (above < need && above + c >= need) {
-    st->prefix |= uint32_t(b) << (24 - 8 * pass);
-    st->need = need - above;
-  }
+  if (quarter != 0) return;
+  c += hs[kPer][b] + hs[2 * kPer][b] + hs[3 * kPer][b];
+  if (c) atomicAdd(&st->hist[pass][b], c);
 }
 
 // Sixteen consecutive elements of thread t of chunk `chunk`: t * 16 ..
@@ -243,10 +273,11 @@ __device__ __forceinline__ uint32_t grid_block_scan(uint32_t v, uint32_t* wsum, 
 
 __global__ __launch_bounds__(kGT) void select_count_kernel(const float* __restrict__ scores,
     const float* __restrict__ delta, int64_t N,
-                                                           const SelState* __restrict__ st,
+                                                           SelState* __restrict__ st,
                                                            uint32_t* __restrict__ cnt) {
   __shared__ uint32_t wsum[kGWaves];
-  const uint32_t T = st->prefix;
+  uint32_t T, need;
+  select_pick(st, 4, T, need);
   const int64_t i0 = int64_t(blockIdx.x) * kChunk + 16 * threadIdx.x;
   uint32_t key[16];
   bool live[16];
@@ -271,7 +302,7 @@ __global__ __launch_bounds__(kThreads) void select_offsets_kernel(const uint32_t
                                                                   uint32_t* __restrict__ off) {
   constexpr int kPer = 4;
   __shared__ uint32_t wsum[kWaves];
-  const uint32_t need = st->need;
+  const uint32_t need = st->need[4];
   uint32_t eq_before = 0u, out_before = 0u;
   for (int c0 = 0; c0 < nchunks; c0 += kThreads * kPer) {
     const int cb = c0 + kPer * threadIdx.x;
@@ -309,16 +340,19 @@ __global__ __launch_bounds__(kThreads) void select_offsets_kernel(const uint32_t
 // Chunk = 4 waves x 4 rounds x 256 consecutive elements (4 per lane, one
 // 16-byte load).  Counts per wave first (keys stay in registers), a 4-entry
 // scan in LDS, then each round ranks its lanes with a wave scan, so
-// neighbouring lanes store neighbouring output positions.
+// neighbouring lanes store neighbouring output positions.  SUM: the workgroup
+// sums the counts (`per`) of the chunks before it; otherwise `per` holds its
+// offset and quota.
+template <bool SUM>
 __global__ __launch_bounds__(kGT) void select_emit_kernel(const float* __restrict__ scores,
-    const float* __restrict__ delta, int64_t N,
+                                                          const float* __restrict__ delta, int64_t N,
                                                           const SelState* __restrict__ st,
-                                                          const uint32_t* __restrict__ off, int64_t k,
+                                                          const uint32_t* __restrict__ per, int64_t k,
                                                           int32_t* __restrict__ idx) {
   constexpr int kRounds = kChunk / kGT / 4;  // 4
-  __shared__ uint32_t wcnt[kGWaves];
+  __shared__ uint32_t wcnt[kGWaves], wgt[kGWaves], weq[kGWaves];
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-  const uint32_t T = st->prefix;
+  const uint32_t T = st->prefix[4];
   const int64_t w0 = int64_t(blockIdx.x) * kChunk + int64_t(wave) * kRounds * 4 * kWave;
   uint32_t key[kRounds][4];
   bool live[kRounds][4];
@@ -330,12 +364,39 @@ __global__ __launch_bounds__(kGT) void select_emit_kernel(const float* __restric
     for (int e = 0; e < 4; ++e) packed += live[r][e] ? ((key[r][e] > T) << 16) | uint32_t(key[r][e] == T) : 0u;
   }
   packed = wave_sum_u32(packed);
+  if constexpr (SUM) {
+    uint32_t gt = 0u, eq = 0u;
+    for (unsigned c = tid; c < blockIdx.x; c += kGT) {
+      gt += per[2 * c];
+      eq += per[2 * c + 1];
+    }
+    gt = wave_sum_u32(gt);
+    eq = wave_sum_u32(eq);
+    if (lane == 0) {
+      wgt[wave] = gt;
+      weq[wave] = eq;
+    }
+  }
   if (lane == 0) wcnt[wave] = packed;
   __syncthreads();
   uint32_t before = 0u;  // this chunk's keys before this wave, packed
   for (int w = 0; w < wave; ++w) before += wcnt[w];
   uint32_t gt_b = before >> 16, eq_b = before & 0xffffu;
-  const uint32_t base = off[2 * blockIdx.x], take = off[2 * blockIdx.x + 1];
+  uint32_t base, take;  // this chunk's first output position, and its quota of keys == T
+  if constexpr (SUM) {
+    uint32_t gt = 0u, eq = 0u;
+#pragma unroll
+    for (int w = 0; w < kGWaves; ++w) {
+      gt += wgt[w];
+      eq += weq[w];
+    }
+    const uint32_t need = st->need[4];
+    base = gt + min(eq, need);
+    take = need - min(eq, need);
+  } else {
+    base = per[2 * blockIdx.x];
+    take = per[2 * blockIdx.x + 1];
+  }
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
     uint32_t mine = 0u;
@@ -422,16 +483,18 @@ static int select_impl(const float* scores, const float* delta, int64_t N, int64
                      need.bytes, (long long)N);
   const SelWs ws = select_ws_layout(static_cast<char*>(workspace), N);
   const int nchunks = int((N + kChunk - 1) / kChunk);
-  const int hblocks = int(std::min<int64_t>(kHistBlocks, (N + 4 * kGT * 8 - 1) / (4 * kGT * 8)));
+  const int hblocks = int(std::min<int64_t>(kHistBlocks, (N + kHistKeys - 1) / kHistKeys));
   TimedLaunch timed("select", s);
   hipLaunchKernelGGL(select_init_kernel, dim3(1), dim3(kGT), 0, s, ws.st, uint32_t(k));
-  for (int pass = 0; pass < 4; ++pass) {
-    hipLaunchKernelGGL(select_hist_kernel, dim3(hblocks), dim3(kGT), 0, s, scores, delta, N, pass, ws.st);
-    hipLaunchKernelGGL(select_scan_kernel, dim3(1), dim3(256), 0, s, pass, ws.st);
-  }
+  for (int pass = 0; pass < 4; ++pass)
+    hipLaunchKernelGGL(select_hist_kernel, dim3(hblocks), dim3(kHT), 0, s, scores, delta, N, pass, ws.st);
   hipLaunchKernelGGL(select_count_kernel, dim3(nchunks), dim3(kGT), 0, s, scores, delta, N, ws.st, ws.cnt);
-  hipLaunchKernelGGL(select_offsets_kernel, dim3(1), dim3(kThreads), 0, s, ws.cnt, nchunks, ws.st, ws.off);
-  hipLaunchKernelGGL(select_emit_kernel, dim3(nchunks), dim3(kGT), 0, s, scores, delta, N, ws.st, ws.off, k, idx);
+  if (nchunks <= kSumChunks) {
+    hipLaunchKernelGGL(select_emit_kernel<true>, dim3(nchunks), dim3(kGT), 0, s, scores, delta, N, ws.st, ws.cnt, k, idx);
+  } else {
+    hipLaunchKernelGGL(select_offsets_kernel, dim3(1), dim3(kThreads), 0, s, ws.cnt, nchunks, ws.st, ws.off);
+    hipLaunchKernelGGL(select_emit_kernel<false>, dim3(nchunks), dim3(kGT), 0, s, scores, delta, N, ws.st, ws.off, k, idx);
+  }
   return launch_status("select");
 }
 
