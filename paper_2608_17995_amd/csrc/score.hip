@@ -316,30 +316,29 @@ __global__ __launch_bounds__(256) void spatial_f32_kernel(const float* __restric
   f32x4 qf[kC], kf[kC];
 #pragma unroll
   for (int j = 0; j < kC; ++j) qf[j] = load4u(q + (int64_t(rc) * H + h) * DH + 16 * j + 4 * g);
-  const float l = lse[int64_t(h) * N + rc], scale = rsqrtf(float(DH));
+  const double l = lse[int64_t(h) * N + rc], scale = 1.0 / sqrt(double(DH));
   // Keys past the last repeat it and are not counted.
   auto load_k = [&](int k0) {
 #pragma unroll
     for (int j = 0; j < kC; ++j) kf[j] = load4u(ktxt + (int64_t(min(k0 + l16, L - 1)) * H + h) * DH + 16 * j + 4 * g);
   };
-  double acc = 0.0;  // the min-max normalisation magnifies what the extreme rows lose
+  // The min-max normalisation magnifies what the extreme rows lose, so beyond
+  // 16 products everything is in 64 bits.
+  double acc = 0.0;
   load_k(0);
   for (int k0 = 0; k0 < L; k0 += 16) {
-    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int j = 0; j < kC; ++j)
+    for (int j = 0; j < kC; ++j) {
+      f32x4 t = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int e = 0; e < 4; ++e) s = mfma16x16x4(kf[j][e], qf[j][e], s);
+      for (int e = 0; e < 4; ++e) t = mfma16x16x4(kf[j][e], qf[j][e], t);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s[r] += t[r];
+    }
     if (k0 + 16 < L) load_k(k0 + 16);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      // exp(x - l), with what the difference loses to rounding (up to 5e-7 at the
-      // usual l of 8 to 16, times e) put back.
-      const float x = s[r] * scale, t = x - l, back = t - x;
-      const float lost = (x - (t - back)) - (l + back);
-      const float e = expf(t);
-      acc += k0 + 4 * g + r < L ? double(fabsf(t) < INFINITY ? fmaf(e, lost, e) : e) : 0.0;
-    }
+    for (int r = 0; r < 4; ++r) acc += k0 + 4 * g + r < L ? exp(s[r] * scale - l) : 0.0;
   }
   acc += __shfl_xor(acc, 16);
   acc += __shfl_xor(acc, 32);
@@ -400,10 +399,10 @@ __global__ __launch_bounds__(256) void temporal_kernel(const T* __restrict__ ft,
       }
     }
     s = wave_sum(s);
-    float ah = 0.f;
-    for (int h = lane; h < H; h += kWave) ah += part[int64_t(h) * N + i];
-    ah = wave_sum(ah);
-    const float A = ah / float(H);
+    double ah = 0.0;
+#pragma unroll 4
+    for (int h = 0; h < H; ++h) ah += part[int64_t(h) * N + i];
+    const float A = float(ah / H);
     const float V = s / (2.f * float(Df));
     if (lane == 0) {
       a_out[i] = A;
