@@ -1146,16 +1146,17 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmArgs a, co
 // Bound by: latency.  The fp32 block of 288 rows and width 256 has 20 to 80
 // tiles of 64 x 64, each a serial loop over K on one CU of 256; tiles of 32 x 32
 // with K over eight waves take four times the CUs and an eighth of the chain.
-// Measured against the 64 x 64 kernel: 288 x 768 x 256 18.9 -> 9.4 us, 288 x 256 x
-// 1024 58.7 -> 12.8, 1024 x 384 x 1536 98 -> 30; error against 64 bits (relative,
+// Measured against the 64 x 64 kernel: 288 x 768 x 256 18.9 -> 9.2 us, 288 x 256 x
+// 1024 58.7 -> 11.9, 1024 x 384 x 1536 98 -> 30; error against 64 bits (relative,
 // 2-norm) 2.9e-7 -> 1.2e-7 at K = 256, 5.7e-7 -> 2.1e-7 at 1024.
 constexpr int kFT = 32, kFK = 16, kFWaves = 8;
 __global__ __launch_bounds__(64 * kFWaves) void gemm_f32_kernel(const GemmArgs a) {
   constexpr int kP = kFT + 4, U = 2;
   __shared__ __attribute__((aligned(16))) float red[kFWaves][kFT * kP];
-  int prob, ks;
-  int64_t m0, n0;
-  if (!map_tile(a, kFT, kFT, 1, prob, m0, n0, ks)) return;
+  int prob, tm, tn;  // 32-bit arithmetic: 64-bit divisions took about 1 us of the launch
+  pp_place(xcd_logical_id32(blockIdx.x, gridDim.x), uint32_t((a.N + kFT - 1) / kFT),
+           uint32_t((a.p[0].M + kFT - 1) / kFT), a.nprob > 1 ? uint32_t((a.p[1].M + kFT - 1) / kFT) : 0u, prob, tm, tn);
+  const int64_t m0 = int64_t(tm) * kFT, n0 = int64_t(tn) * kFT;
   const GemmProblem p = prob ? a.p[1] : a.p[0];  // by value: a select, no indexed copy of the arguments
   const int tid = threadIdx.x, lane = tid % kWave, l32 = lane % 32, hi = lane / 32;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
