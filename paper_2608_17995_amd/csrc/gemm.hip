@@ -1083,7 +1083,9 @@ __global__ __launch_bounds__(256) void tail_reduce_kernel(const GemmArgs a, cons
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = k == 0 ? x[e] : v[e] + x[e];
     }
-    epilogue8(a, p, m, n, v);
+    GemmProblem pg = p;
+    if (a.mod.B) pg.gate = static_cast<const bf16_t*>(p.gate) + mod_offset(a.mod, p.row0 + m);  // this row's image
+    epilogue8(a, pg, m, n, v);
   }
   const int r8 = r & ~7, tc = int(threadIdx.x);
   const int64_t mt = int64_t(row) * kBM + r8, nt = int64_t(col) * BN + tc;

@@ -79,8 +79,8 @@ struct GemmArgs {
   int mode0, mode1, mode2;
   // Per-image gates (EPI_RESID_GATE) and post-LN modulation: row m of
   // problem p takes gate + mod_offset(mod, p.row0 + m) (in the ping-pong
-  // kernel's epilogue or a split-K reduce; launch_gemm runs the general
-  // kernel split for it).
+  // kernel's epilogue, the split tail's reduce or a split-K reduce; launch_gemm
+  // runs the general kernel split for it).
   ModRows mod;
 };
 

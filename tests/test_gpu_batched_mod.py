@@ -35,11 +35,15 @@ def _inputs(w, n_txt, n_img, seed):
     return x, pos
 
 
-def _per_image_mods(base, B, seed, dtype):
+def _per_image_mods(base, B, seed, dtype, gate_std=0.0):
     """B modulation blocks [B, n_vec, D] around `base` (shifts and scales
-    moved by N(0, 0.3), gates by N(0, 0.3) around theirs), bf16-rounded."""
+    moved by N(0, 0.3), gates by N(0, 0.3) around theirs, and by N(0, gate_std)
+    more), bf16-rounded."""
     g = np.random.default_rng(seed)
-    return np.stack([G.round_to(base + g.normal(0.0, 0.3, base.shape), dtype) for _ in range(B)])
+    m = np.stack([base + g.normal(0.0, 0.3, base.shape) for _ in range(B)])
+    if gate_std:
+        m[:, 2::3] += g.normal(0.0, gate_std, m[:, 2::3].shape)
+    return np.stack([G.round_to(b, dtype) for b in m])
 
 
 def _rows_of(b, txt_off, img_off):
@@ -47,10 +51,10 @@ def _rows_of(b, txt_off, img_off):
     return np.concatenate([np.arange(txt_off[b], txt_off[b + 1]), T + np.arange(img_off[b], img_off[b + 1])])
 
 
-def _setup(gpu, w, kind, B, seed):
+def _setup(gpu, w, kind, B, seed, gate_std=0.0):
     if kind == "double":
         wt, wi = G.double_stream_weights(w, 0, 0), G.double_stream_weights(w, 0, 1)
-        mt, mi = _per_image_mods(wt["mod"], B, seed, w.dtype), _per_image_mods(wi["mod"], B, seed + 1, w.dtype)
+        mt, mi = (_per_image_mods(t["mod"], B, seed + i, w.dtype, gate_std) for i, t in enumerate((wt, wi)))
         dt, di = double_weights_dev(wt, w.dtype), double_weights_dev(wi, w.dtype)
         dt["mod"], di["mod"] = dev(mt.reshape(-1, w.D), w.dtype), dev(mi.reshape(-1, w.D), w.dtype)
         bw = gpu.BlockWeights(gpu.BLOCK_DOUBLE, txt=dt, img=di)
@@ -61,7 +65,7 @@ def _setup(gpu, w, kind, B, seed):
             return out, lse
         return bw, stride, oracle_image, (dt, di)
     ws_ = G.single_block_weights(w, 0)
-    ms = _per_image_mods(ws_["mod"], B, seed, w.dtype)
+    ms = _per_image_mods(ws_["mod"], B, seed, w.dtype, gate_std)
     ds = double_weights_dev(ws_, w.dtype)
     ds["mod"] = dev(ms.reshape(-1, w.D), w.dtype)
     bw = gpu.BlockWeights(gpu.BLOCK_SINGLE, single=ds)
@@ -98,6 +102,86 @@ def test_block_batched_per_image_modulation(gpu, kind):
     torch.cuda.synchronize()
     np.testing.assert_array_equal(host(o0), host(o1))
     assert not np.array_equal(host(o0), got)   # the per-image modulation did change the result
+
+
+# Unsplit (the gates in the GEMM's epilogue), in two and three k splits (in the
+# reduce), with every tile or the last one in a split tail (in the tail's
+# reduce), the 128-wide form, and the general kernel.
+GATED_PLANS = ["256,1", "256,2", "256,3", "256,1,8,1,100,2", "256,1,8,1,1,3", "128,1,8,1", "128,2,8,1", "128,1,8,2"]
+
+
+@pytest.mark.parametrize("plan", GATED_PLANS)
+@pytest.mark.parametrize("kind", ["double", "single"])
+def test_per_image_gates_under_every_plan(gpu, monkeypatch, kind, plan):
+    # Gates that differ by O(1) between images whose rows end inside a tile:
+    # another image's gate anywhere is far outside the bar.
+    for family in ("gemm_o", "gemm_mlp_out", "gemm_single_out"):
+        monkeypatch.setenv(f"AVITS_GEMM_TILE_{family}", plan)
+    w = C.TINY_BF16
+    txt, img = [32, 0, 7, 129], [200, 77, 1, 64]
+    txt_off, img_off = _layout(txt, img)
+    x, pos = _inputs(w, txt_off[-1], img_off[-1], seed=31)
+    bw, stride, oracle_image, keep = _setup(gpu, w, kind, len(txt), seed=41, gate_std=1.0)
+    t_x = dev(x, w.dtype)
+    out = torch.empty_like(t_x)
+    gpu.avits_block_forward_batched_ex(t_x, out, dev(pos), txt_off, img_off, bw, w.H, stride)
+    torch.cuda.synchronize()
+    got = host(out)
+    for b in range(len(txt)):
+        rows = _rows_of(b, txt_off, img_off)
+        ref, _ = oracle_image(x, pos, txt_off, img_off, b)
+        assert_close(got[rows] - x[rows], ref[rows] - x[rows], w.dtype, f"image {b} update ({kind}, {plan})")
+
+
+# Batches of ordinary size whose default plan splits only the tiles past the last
+# full round (264 to 336 tiles of 256 x 256), against the same block unsplit: the
+# order of the fp32 sums alone differs, so the update differs by single bf16
+# roundings of the intermediates, far less than by any other image's gate.
+@pytest.mark.parametrize("kind,B,L,n", [("double", 2, 512, 2500), ("double", 3, 512, 1400), ("single", 3, 128, 1741),
+                                        ("single", 4, 512, 1229)])
+def test_per_image_gates_default_tail(gpu, monkeypatch, kind, B, L, n):
+    H, d = 24, 128
+    D = H * d
+    F = 4 * D
+    g = torch.Generator(device="cuda").manual_seed(B * 1000 + n)
+    f = lambda *s, std=1.0: (torch.randn(*s, device="cuda", generator=g) * std).bfloat16()  # noqa: E731
+
+    def mod(vectors):
+        m = f(B, vectors, D, std=0.1)
+        m[:, 2::3] = f(B, vectors // 3, D)
+        return m.view(B * vectors, D)
+
+    if kind == "double":
+        def stream():
+            return dict(mod=mod(6), w_qkv=f(3 * D, D, std=0.02), b_qkv=f(3 * D, std=0.02), g_q=1 + f(d, std=0.02),
+                        g_k=1 + f(d, std=0.02), w_o=f(D, D, std=0.02), b_o=f(D, std=0.02), w_mlp1=f(F, D, std=0.02),
+                        b_mlp1=f(F, std=0.02), w_mlp2=f(D, F, std=0.02), b_mlp2=f(D, std=0.02))
+        bw, stride = gpu.BlockWeights(gpu.BLOCK_DOUBLE, txt=stream(), img=stream()), 6 * D
+    else:
+        one = dict(mod=mod(3), w_in=f(3 * D + F, D, std=0.02), b_in=f(3 * D + F, std=0.02), g_q=1 + f(d, std=0.02),
+                   g_k=1 + f(d, std=0.02), w_out=f(D, D + F, std=0.02), b_out=f(D, std=0.02))
+        bw, stride = gpu.BlockWeights(gpu.BLOCK_SINGLE, single=one), 3 * D
+    txt_off, img_off = _layout([L] * B, [n] * B)
+    S = txt_off[-1] + img_off[-1]
+    x = f(S, D)
+    i = torch.arange(S, device="cuda", dtype=torch.int32)
+    pos = torch.stack([torch.zeros_like(i), i // 64 % 64, i % 64], 1).contiguous()
+    ws = torch.empty(gpu.avits_block_workspace_bytes(bw.kind, S, H, d, F, gpu.BF16), dtype=torch.uint8, device="cuda")
+    out = []
+    for plan in (None, "256,1"):
+        for family in ("gemm_o", "gemm_mlp_out", "gemm_single_out"):
+            if plan:
+                monkeypatch.setenv(f"AVITS_GEMM_TILE_{family}", plan)
+        y = torch.empty_like(x)
+        gpu.avits_block_forward_batched_ex(x, y, pos, txt_off, img_off, bw, H, stride, workspace=ws)
+        out.append(y.double() - x.double())
+    torch.cuda.synchronize()
+    default, unsplit = out
+    assert torch.isfinite(default).all()
+    # Per 256-row tile, so that one wrong tile is not lost in the whole.
+    worst = max(float((default[r:r + 256] - unsplit[r:r + 256]).norm() / unsplit[r:r + 256].norm())
+                for r in range(0, S, 256))
+    assert worst <= 2.0 ** -7, worst
 
 
 @pytest.mark.parametrize("kind", ["double", "single"])
