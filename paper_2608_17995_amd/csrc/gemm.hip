@@ -1416,6 +1416,8 @@ int launch_gemm(const GemmArgs& a, int dtype, hipStream_t s, const char* family,
                 size_t partial_bytes, GemmPostLN* post_ln) {
   GemmPlan pl = plan_gemm(a, dtype, partial ? partial_bytes : 0, family, post_ln != nullptr);
   if (pl.tiles == 0) return AVITS_OK;
+  if (a.mod.B > 0 && a.mode0 == EPI_RESID_GATE && dtype != AVITS_BF16)
+    return set_error(AVITS_ERR_UNSUPPORTED, "gemm %s: per-image gates need bf16", family ? family : "");
   // The general kernel's epilogue has one gate per launch: there, per-image
   // gates are applied by the split-K reduce and such a projection runs split.
   const bool per_image_gate = a.mod.B > 0 && a.mode0 == EPI_RESID_GATE && pl.stages == 2;
@@ -1432,8 +1434,6 @@ int launch_gemm(const GemmArgs& a, int dtype, hipStream_t s, const char* family,
     pl.splits = 1;
     pl.tail = 0;
   }
-  if (per_image_gate && dtype != AVITS_BF16)
-    return set_error(AVITS_ERR_UNSUPPORTED, "gemm %s: per-image gates need bf16", family ? family : "");
   if (dtype == AVITS_BF16) {
     {
       TimedLaunch timed(family, s);  // the GEMM kernel alone; the reduce is its own family

@@ -352,3 +352,35 @@ def test_position_and_noise_validation(lib):
     assert lib.avits_noise_bits(-1, 4, 8, 1, FAKE, None) == INVALID
     assert lib.avits_noise_bits(0, 4, 6, 1, FAKE, None) == INVALID
     assert lib.avits_noise_bits(0, 0, 8, 1, None, None) == 0
+
+
+def test_gemm_refuses_per_image_gates_in_fp32(lib):
+    # launch_gemm (kernels.h) directly: the batched block refuses fp32 before it,
+    # so no entry point reaches this check.  The fp32 kernels know one gate.
+    import ctypes as ct
+
+    class Problem(ct.Structure):
+        _fields_ = [("A", ct.c_void_p), ("lda", ct.c_int64), ("W", ct.c_void_p), ("bias", ct.c_void_p), ("M", ct.c_int64),
+                    ("out0", ct.c_void_p), ("ld0", ct.c_int64), ("out1", ct.c_void_p), ("ld1", ct.c_int64),
+                    ("out2", ct.c_void_p), ("ld2", ct.c_int64), ("resid", ct.c_void_p), ("ldr", ct.c_int64),
+                    ("gate", ct.c_void_p), ("scat", ct.c_void_p), ("scat_idx", ct.c_void_p), ("scat_row0", ct.c_int64),
+                    ("scat_ld", ct.c_int64), ("scat_n", ct.c_int64), ("row0", ct.c_int64)]
+
+    class Mod(ct.Structure):
+        _fields_ = [("B", ct.c_int32), ("stride", ct.c_int64), ("end", ct.c_int64 * 32)]
+
+    class Args(ct.Structure):
+        _fields_ = [("p", Problem * 2), ("nprob", ct.c_int), ("N", ct.c_int64), ("K", ct.c_int64), ("n_split", ct.c_int64),
+                    ("n_split2", ct.c_int64), ("mode0", ct.c_int), ("mode1", ct.c_int), ("mode2", ct.c_int), ("mod", Mod)]
+
+    out = subprocess.run(["nm", "-D", "--defined-only", avits.lib_path()], capture_output=True, text=True).stdout
+    launch = getattr(ct.CDLL(avits.lib_path()), re.search(r"\bT (_ZN5avits11launch_gemm\w+)", out).group(1))
+    launch.argtypes = [ct.c_void_p, ct.c_int, ct.c_void_p, ct.c_char_p, ct.c_void_p, ct.c_size_t, ct.c_void_p]
+    a = Args(nprob=1, N=64, K=64, n_split=64, n_split2=64, mode0=2)  # EPI_RESID_GATE
+    a.p[0].M = 10
+    a.mod.B = 2
+    for partial in (None, FAKE):
+        assert launch(ct.addressof(a), 0, None, b"gemm_o", partial, 1 << 30 if partial else 0, None) == UNSUPPORTED
+        assert b"per-image gates" in lib.avits_last_error()
+    a.p[0].M = 0   # nothing to do
+    assert launch(ct.addressof(a), 0, None, b"gemm_o", None, 0, None) == 0
