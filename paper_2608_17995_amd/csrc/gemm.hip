@@ -934,16 +934,18 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmArgs args, 
     const uint32_t a_dst = lds0 + a_half * 128 + sub * 1024;
     const uint32_t w_dst = lds0 + RA * kA * 16 + w_half * 128 + sub * 1024;
     // This wave's share of k-tile t of A or W, into a slot of its ring.  Past
-    // the last k-tile the resource's range is 0: no memory is read, and the
-    // loads still count, so every wait below is the same constant.
+    // the last k-tile the resource's range and the scalar offset are 0: every
+    // offset is out of range (also where the range is taken less the scalar
+    // offset, which then may not exceed it), no memory is read, and the loads
+    // still count, so every wait below is the same constant.
     auto load_a = [&](int t, int slot) {
-      const uint32_t koff = uint32_t(kt0 + t) * (kBK * 2);
+      const uint32_t koff = t < n_t ? uint32_t(kt0 + t) * (kBK * 2) : 0u;
       const u32x4 r = {ra[0], ra[1], t < n_t ? ra[2] : 0u, ra[3]};
 #pragma unroll
       for (int j = 0; j < LA; ++j) lds_load16(a_dst + slot * (kA * 16), a_off[j], r, koff, 4096 * j);
     };
     auto load_w = [&](int t, int slot) {
-      const uint32_t koff = uint32_t(kt0 + t) * (kBK * 2);
+      const uint32_t koff = t < n_t ? uint32_t(kt0 + t) * (kBK * 2) : 0u;
       const u32x4 r = {rw[0], rw[1], t < n_t ? rw[2] : 0u, rw[3]};
 #pragma unroll
       for (int j = 0; j < LW; ++j) lds_load16(w_dst + slot * (kW * 16), w_off[j], r, koff, 4096 * j);
