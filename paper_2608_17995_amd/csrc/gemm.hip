@@ -6,12 +6,12 @@
 //    per SIMD hide each other's LDS and barrier waits.  Operands on 16-byte
 //    boundaries run the ping-pong form (gemm_bf16_pp_kernel, BN 256 or 128,
 //    16x16x32 products): the two halves of the workgroup alternate compute and
-//    memory phases.  Others run gemm_bf16_kernel (BN 128, 32x32x16 products).
+//    memory phases.  Others run the register-staged kernels on 32x32x16 products:
+//    gemm_bf16_staged_kernel (BN 256, ping-pong too) or gemm_bf16_kernel (BN 128).
 //  - The MFMA computes C^T = W A^T, so each lane owns groups of four
 //    consecutive output columns of one row (8-byte stores in the epilogue).
 //  - k-tiles are staged global -> LDS: directly in the ping-pong kernel, through
-//    registers and two LDS buffers in the general one (one barrier per k-tile:
-//    while tile t is multiplied, tiles t+1 and t+2 are in flight).  LDS rows
+//    registers and two LDS buffers in the register-staged ones.  LDS rows
 //    are 128 bytes (64 bf16) with the 16-byte chunk index XOR-swizzled by
 //    (row / 2) mod 8, which makes both the staging writes and the 16-byte
 //    fragment reads of 16 consecutive rows bank-conflict free.
@@ -442,7 +442,8 @@ __device__ __forceinline__ void staged_epilogue(const GemmArgs& a, const GemmPro
 // Swizzled 16-byte chunk slot of (row, chunk) in a 128-byte LDS row.
 __device__ __forceinline__ int swz(int row, int chunk) { return row * 8 + (chunk ^ ((row >> 1) & 7)); }
 
-// The general kernel: 256 x 128 tiles, any alignment.
+// The 128-wide register-staged kernel: any alignment, one barrier per k-tile (while
+// tile t is multiplied, tiles t + 1 and t + 2 are in flight).
 __global__ __launch_bounds__(512) void gemm_bf16_kernel(const GemmArgs a, float* __restrict__ partial, int splits) {
   constexpr int BN = 128, WAVES_M = 2, WAVES_N = 4;
   constexpr int NT = 64 * WAVES_M * WAVES_N;
@@ -1055,6 +1056,180 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmArgs args, 
   }
 }
 
+// Register-staged ping-pong form, 256 x 256 x 64 on 32x32x16 products, for
+// operands off the 16-byte grid: loads that go to LDS directly want 16-byte
+// boundaries, loads to registers and the epilogue through LDS in fp32 do not.
+// The two groups of four waves (rows 0 .. 127 and 128 .. 255) alternate between
+// a compute phase (the 32 MFMAs of one k-tile, fragments read from LDS) and a
+// memory phase (stage half of a later k-tile into LDS and issue the loads of the
+// half after it), one workgroup barrier per phase, offset by one phase:
+//   phase 2t:     group 0 computes k-tile t;  group 1 stages its half of
+//                 tile t + 1 and loads its half of tile t + 2;
+//   phase 2t + 1: group 1 computes k-tile t;  group 0 stages / loads the same.
+// Tile t lives in LDS buffer t mod 2: it is read in phases 2t and 2t + 1 and
+// written in phases 2t - 2 and 2t - 1, after tile t - 2 left that buffer.
+// Bound by LDS: fragment reads between the MFMAs and the staging writes.  With every
+// bias one element off, against the 128-wide kernel, unsplit: 1741 x 9216 x
+// 3072 127 -> 97 us, 4096 x 3072 x 12288 423 -> 287, a double block of 845 rows 568 ->
+// 388, of 1741 667 -> 545, of 4608 1682 -> 1377.
+__global__ __launch_bounds__(512) void gemm_bf16_staged_kernel(const GemmArgs a, float* __restrict__ partial,
+                                                              int splits, int tail, int tsp) {
+  constexpr int BN = 256, WM = 128, WN = 64;
+  constexpr int TM = WM / 32, TN = WN / 32;
+  constexpr int HALF = 4;                    // 16-byte chunks per thread per half-tile operand
+  __shared__ u32x4 lds[2][(kBM + BN) * 8];
+
+  // Whole tiles (or every tile's k splits) first, then the split tail's units,
+  // each class renumbered for the XCDs; tiles placed as in the kernel above, which
+  // the tail's reduce relies on.
+  const uint32_t tn_all = uint32_t((a.N + BN - 1) / BN), tm0 = uint32_t((a.p[0].M + kBM - 1) / kBM);
+  const uint32_t tm1 = a.nprob > 1 ? uint32_t((a.p[1].M + kBM - 1) / kBM) : 0u;
+  const uint32_t whole = tail ? tn_all * (tm0 + tm1) - uint32_t(tail) : gridDim.x;
+  const bool split_tail = blockIdx.x >= whole;
+  const uint32_t v = split_tail ? xcd_logical_id32(blockIdx.x - whole, gridDim.x - whole)
+                                : xcd_logical_id32(blockIdx.x, whole);
+  const int nsp = split_tail ? tsp : splits, ks = int(v % uint32_t(nsp));
+  const int tidx = split_tail ? int(v / uint32_t(nsp)) : -1;
+  int prob, tm, tn;
+  pp_place((split_tail ? whole : 0) + v / uint32_t(nsp), tn_all, tm0, tm1, prob, tm, tn);
+  const int64_t m0 = int64_t(tm) * kBM, n0 = int64_t(tn) * BN;
+  const GemmProblem p = prob ? a.p[1] : a.p[0];  // by value: a select, no indexed copy of the arguments
+  const bf16_t* A = static_cast<const bf16_t*>(p.A);
+  const bf16_t* W = static_cast<const bf16_t*>(p.W);
+  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+  const int l32 = lane % 32, hi = lane / 32;
+  const int grp = __builtin_amdgcn_readfirstlane(wave / 4);
+  const int wm = grp, wn = wave % 4;
+
+  const int64_t nk = a.K / kBK;
+  const int64_t kt0 = nk * ks / nsp, kt1 = nk * (ks + 1) / nsp;
+  const int64_t n_t = kt1 - kt0;
+
+  // Staging of this group's half: A rows and W rows [128 grp, 128 grp + 128),
+  // thread tg moves chunk tg % 8 of rows tg / 8 + 32 j (one swizzle for all j).
+  const int tg = tid % 256;
+  const int row_t = tg / 8, kc_t = tg % 8;
+  const int slot_t = (128 * grp + row_t) * 8 + (kc_t ^ ((row_t >> 1) & 7));
+  uint32_t a_off[HALF], w_off[HALF];
+#pragma unroll
+  for (int j = 0; j < HALF; ++j) {
+    a_off[j] = uint32_t(((128 * grp + row_t + 32 * j) * p.lda + kc_t * 8) * 2);
+    w_off[j] = uint32_t(((128 * grp + row_t + 32 * j) * a.K + kc_t * 8) * 2);
+  }
+  const char* a_base = reinterpret_cast<const char*>(A + m0 * p.lda);
+  const char* w_base = reinterpret_cast<const char*>(W + n0 * a.K);
+  const int64_t a_bytes = (p.M - m0) * p.lda * 2, w_bytes = (a.N - n0) * a.K * 2;
+  // The staged loads stay in flight across the group's next compute phase
+  // (a loop-carried value), so they are compiler-visible buffer loads: the
+  // compiler places the vmcnt wait before the LDS store that consumes them.
+  u32x4 sa[HALF], sw[HALF];
+  auto load_half = [&](int64_t kt) {
+    const int64_t koff = kt * kBK * 2;
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char*>(a_base + koff), 0, int(range32(a_bytes - koff)), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char*>(w_base + koff), 0, int(range32(w_bytes - koff)), 0x00020000);
+#pragma unroll
+    for (int j = 0; j < HALF; ++j) sa[j] = __builtin_amdgcn_raw_buffer_load_b128(ra, int(a_off[j]), 0, 0);
+#pragma unroll
+    for (int j = 0; j < HALF; ++j) sw[j] = __builtin_amdgcn_raw_buffer_load_b128(rw, int(w_off[j]), 0, 0);
+  };
+  auto store_half = [&](int buf) {
+#pragma unroll
+    for (int j = 0; j < HALF; ++j) lds[buf][slot_t + 256 * j] = sa[j];
+#pragma unroll
+    for (int j = 0; j < HALF; ++j) lds[buf][kBM * 8 + slot_t + 256 * j] = sw[j];
+  };
+
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  auto compute = [&](int buf) {
+    const u32x4* L = lds[buf];
+    bf16x8 af[2][TM], wf[2][TN];
+    // Fragments are read in the order the next k step's MFMAs (i-major)
+    // consume them, so the first MFMAs wait on the oldest reads.
+    auto read = [&](int kk, int slot) {
+      const int chunk = 2 * kk + hi;
+      wf[slot][0] = as_bf16x8(L[kBM * 8 + swz(wn * WN + l32, chunk)]);
+      af[slot][0] = as_bf16x8(L[swz(wm * WM + l32, chunk)]);
+#pragma unroll
+      for (int j = 1; j < TN; ++j) wf[slot][j] = as_bf16x8(L[kBM * 8 + swz(wn * WN + 32 * j + l32, chunk)]);
+#pragma unroll
+      for (int i = 1; i < TM; ++i) af[slot][i] = as_bf16x8(L[swz(wm * WM + 32 * i + l32, chunk)]);
+    };
+    read(0, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, TM + TN, 0);
+#pragma unroll
+    for (int kk = 0; kk < kBK / 16; ++kk) {
+      if (kk + 1 < kBK / 16) read(kk + 1, (kk + 1) & 1);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = mfma32x32x16(wf[kk & 1][j], af[kk & 1][i], acc[i][j]);
+      if (kk + 1 < kBK / 16) {
+#pragma unroll
+        for (int r = 0; r < TM + TN; ++r) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - (TM + TN), 0);
+      } else {
+        __builtin_amdgcn_sched_group_barrier(0x008, TM * TN, 0);
+      }
+    }
+  };
+
+  if (n_t > 0) {
+    load_half(kt0);
+    store_half(0);
+    if (n_t > 1) load_half(kt0 + 1);
+  }
+  lds_barrier();
+  // Memory phase of k-tile t: stage this group's half of tile t + 1, then
+  // issue its loads of tile t + 2.
+  auto memory = [&](int64_t t) {
+    if (t + 1 < n_t) {
+      store_half(int((t + 1) & 1));
+      if (t + 2 < n_t) load_half(kt0 + t + 2);
+    }
+  };
+  // Each group runs its own straight loop; both pass the same barriers.
+  if (grp == 0) {
+    for (int64_t t = 0; t < n_t; ++t) {
+      compute(int(t & 1));
+      lds_barrier();
+      memory(t);
+      lds_barrier();
+    }
+  } else {
+    for (int64_t t = 0; t < n_t; ++t) {
+      memory(t);
+      lds_barrier();
+      compute(int(t & 1));
+      lds_barrier();
+    }
+  }
+
+  // Split partials, as in the kernel above.
+  float* pbase = nullptr;
+  int64_t pld = a.N;
+  if (tidx >= 0) {
+    pbase = partial + (int64_t(tidx) * tsp + ks) * (kBM * BN);
+    pld = BN;
+  } else if (splits > 1) {
+    const int64_t rows_all = a.p[0].M + (a.nprob > 1 ? a.p[1].M : 0);
+    pbase = partial + (int64_t(ks) * rows_all + (prob ? a.p[0].M : 0) + m0) * a.N + n0;
+  }
+  staged_epilogue<WM, WN, TM, TN>(a, p, m0, n0, pbase != nullptr, pbase, pld, acc,
+                                  reinterpret_cast<float*>(&lds[0][0]), wave, wm, wn, lane);
+}
+
 // Sum the k splits of each tail tile in split order and apply the epilogue.
 // Block b covers rows 8 (b mod 32) .. + 7 of tail tile b / 32, one thread per
 // eight columns; in a transposed region (the last columns of the QKV
@@ -1265,8 +1440,7 @@ int64_t tiles_of(const GemmArgs& a, int bm, int bn) {
 // What the ping-pong kernel's 16-byte accesses and 64-column strips assume:
 // the library's own buffers and 16-byte aligned tensors always meet it;
 // anything else (a bias that is a slice at an odd element, say) takes the
-// 128-wide kernel, whose accesses are narrower.  A transposed output may
-// start anywhere.
+// register-staged kernels.  A transposed output may start anywhere.
 bool pp_layout_ok(const GemmArgs& a) {
   auto off = [](const void* ptr) { return reinterpret_cast<uintptr_t>(ptr) % 16; };
   if (a.N % 8 != 0 || (a.mod.B > 0 && a.mod.stride % 8 != 0) || (a.n_split < a.N && a.n_split % 64 != 0) || (a.n_split2 < a.N && a.n_split2 % 64 != 0))
@@ -1329,11 +1503,40 @@ GemmPlan plan_gemm(const GemmArgs& a, int dtype, size_t partial_bytes, const cha
   const bool wide = pp_layout_ok(a);
   const int64_t nk = a.K / kBK;
   const int64_t rows = a.p[0].M + (a.nprob > 1 ? a.p[1].M : 0);
-  // The general kernel, where the ping-pong kernel's layout does not hold.
-  pl.bn = 128;
-  pl.stages = 2;
-  pl.tiles = tiles_of(a, kBM, 128);
-  if (wide && pl.tiles > 0) {
+  pl.stages = wide ? 1 : 2;
+  if (tiles_of(a, kBM, 128) == 0) return pl;
+  if (!wide) {
+    // Where that layout does not hold, the register-staged kernels: the largest
+    // busy fraction of the last round of units on the CUs, times a factor per tile
+    // (the 256-wide kernel moves less L2 data per FLOP; measured at the FLUX block
+    // shapes) and one for the partials' traffic of a split.
+    double best = -1.0;
+    auto consider = [&](int bn, double eff, int64_t tiles, double rounds, int splits, int64_t tail, int tsp) {
+      const double score = double(tiles * splits) / kCUs / rounds * eff * (splits > 1 || tail > 0 ? 0.95 : 1.0);
+      if (score <= best + 1e-9) return;
+      best = score;
+      pl.bn = bn;
+      pl.tiles = tiles;
+      pl.splits = splits;
+      pl.tail = tail;
+      pl.tail_splits = tsp;
+    };
+    for (int bn : {256, 128}) {
+      const double eff = bn == 256 ? 1.0 : 0.65;
+      const int64_t t = tiles_of(a, kBM, bn), full = t / kCUs, rem = t % kCUs;
+      for (int sp = 1; sp <= 4; ++sp) {
+        if (sp > 1 && (a.N % 8 != 0 || nk / sp < 4 ||
+                       size_t(sp) * size_t(rows) * size_t(a.N) * sizeof(float) > partial_bytes))
+          break;
+        consider(bn, eff, t, double(ceil_div64(t * sp, kCUs)), sp, 0, 1);
+      }
+      if (bn != 256 || full == 0 || rem == 0 || a.N % 8 != 0) continue;
+      for (int tsp = 2; tsp <= 4; ++tsp) {
+        if (rem * tsp > kCUs || nk / tsp < 4 || size_t(rem * tsp) * kBM * 256 * sizeof(float) > partial_bytes) break;
+        consider(bn, eff, t, double(full) + 1.0 / tsp, 1, rem, tsp);
+      }
+    }
+  } else {
     // The least predicted time over the column tile, the k splits of every
     // tile and the split tail.  A split writes fp32 partials at 4.5 TB/s beside
     // its epilogue and adds a reduce (2 us and its bytes at 4.4 TB/s); where a
@@ -1376,8 +1579,9 @@ GemmPlan plan_gemm(const GemmArgs& a, int dtype, size_t partial_bytes, const cha
     }
   }
   // Tuning override "BN,SPLITS[,8[,STAGES[,TAIL,TSP]]]" (e.g. AVITS_GEMM_TILE=256,3,8,1),
-  // for one launch family with AVITS_GEMM_TILE_<family> (e.g. _gemm_o): BN 256, or 128 with
-  // STAGES 1, the ping-pong kernel, anything else the general one.  TAIL > 0
+  // for one launch family with AVITS_GEMM_TILE_<family> (e.g. _gemm_o): BN 256 or 128,
+  // STAGES 1 (the default at 256) the ping-pong kernel where its layout holds, else
+  // and with 2 (the default at 128) the register-staged one of that width.  TAIL > 0
   // (256-wide tile, SPLITS 1) runs the last min(TAIL, tiles) tiles in TSP k splits.
   const char* env = nullptr;
   if (family) {
@@ -1387,13 +1591,12 @@ GemmPlan plan_gemm(const GemmArgs& a, int dtype, size_t partial_bytes, const cha
   }
   if (!env) env = getenv("AVITS_GEMM_TILE");
   if (env) {
-    int bn = 0, sp = 0, wv = 8, stg = 2, tail = 0, tsp = 1;
+    int bn = 0, sp = 0, wv = 8, stg = 0, tail = 0, tsp = 1;
     const int got = sscanf(env, "%d,%d,%d,%d,%d,%d", &bn, &sp, &wv, &stg, &tail, &tsp);
-    if (got >= 2 && (bn == 256 || bn == 192 || bn == 128) && sp >= 1 && sp <= 4 && wv == 8 &&
-        (stg == 1 || stg == 2)) {
-      const bool pp = wide && (bn == 256 || (bn == 128 && stg == 1));
-      pl.bn = pp ? bn : 128;
-      pl.stages = pp ? 1 : 2;
+    if (got < 4) stg = bn == 256 ? 1 : 2;
+    if (got >= 2 && (bn == 256 || bn == 192 || bn == 128) && sp >= 1 && sp <= 4 && wv == 8 && (stg == 1 || stg == 2)) {
+      pl.bn = bn == 256 ? 256 : 128;
+      pl.stages = wide ? stg : 2;
       pl.splits = sp;
       pl.tiles = tiles_of(a, kBM, pl.bn);
       pl.tail = 0;
@@ -1420,7 +1623,7 @@ int launch_gemm(const GemmArgs& a, int dtype, hipStream_t s, const char* family,
   if (pl.tiles == 0) return AVITS_OK;
   if (a.mod.B > 0 && a.mode0 == EPI_RESID_GATE && dtype != AVITS_BF16)
     return set_error(AVITS_ERR_UNSUPPORTED, "gemm %s: per-image gates need bf16", family ? family : "");
-  // The general kernel's epilogue has one gate per launch: there, per-image
+  // The register-staged kernels' epilogue has one gate per launch: there, per-image
   // gates are applied by the split-K reduce and such a projection runs split.
   const bool per_image_gate = a.mod.B > 0 && a.mode0 == EPI_RESID_GATE && pl.stages == 2;
   if (per_image_gate && (pl.splits < 2 || pl.tail > 0)) {
@@ -1443,7 +1646,10 @@ int launch_gemm(const GemmArgs& a, int dtype, hipStream_t s, const char* family,
       // Ping-pong kernel: equal rounds (a split tail: full rounds, then its own).
       const int64_t rounds = ceil_div64(units, kCUs);
       const dim3 pgrid(unsigned(pl.tail > 0 ? std::min<int64_t>(units, kCUs) : ceil_div64(units, rounds)));
-      if (pl.stages == 2)
+      if (pl.stages == 2 && pl.bn == 256)
+        hipLaunchKernelGGL(gemm_bf16_staged_kernel, dim3(unsigned(units)), dim3(512), 0, s, a, partial, pl.splits,
+                           int(pl.tail), pl.tail_splits);
+      else if (pl.stages == 2)
         hipLaunchKernelGGL(gemm_bf16_kernel, dim3(unsigned(units)), dim3(512), 0, s, a, partial, pl.splits);
       else if (pl.bn == 256)
         hipLaunchKernelGGL(gemm_bf16_pp_kernel<256>, pgrid, dim3(512), 0, s, a, partial, int(units), pl.splits,

@@ -80,14 +80,14 @@ struct GemmArgs {
   // Per-image gates (EPI_RESID_GATE) and post-LN modulation: row m of
   // problem p takes gate + mod_offset(mod, p.row0 + m) (in the ping-pong
   // kernel's epilogue, the split tail's reduce or a split-K reduce; launch_gemm
-  // runs the general kernel split for it).
+  // runs the register-staged kernels split for it).
   ModRows mod;
 };
 
 struct GemmPlan {
   int bn = 0;          // column tile
   int splits = 1;      // K splits (fp32 partials + reduce when > 1)
-  int stages = 1;      // 1: the ping-pong kernel; 2: the general kernel
+  int stages = 1;      // 1: the ping-pong kernel; 2: a register-staged kernel
   int64_t tiles = 0;   // output tiles
   int64_t tail = 0;    // last tiles run in tail_splits k splits (256-wide tile, splits == 1)
   int tail_splits = 1;

@@ -9,6 +9,8 @@ import pytest
 import paper_2608_17995_amd as avits
 from paper_2608_17995_amd import _binding
 
+import _gemm
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER = os.path.join(ROOT, "include", "avits.h")
 
@@ -357,30 +359,31 @@ def test_position_and_noise_validation(lib):
 def test_gemm_refuses_per_image_gates_in_fp32(lib):
     # launch_gemm (kernels.h) directly: the batched block refuses fp32 before it,
     # so no entry point reaches this check.  The fp32 kernels know one gate.
-    import ctypes as ct
-
-    class Problem(ct.Structure):
-        _fields_ = [("A", ct.c_void_p), ("lda", ct.c_int64), ("W", ct.c_void_p), ("bias", ct.c_void_p), ("M", ct.c_int64),
-                    ("out0", ct.c_void_p), ("ld0", ct.c_int64), ("out1", ct.c_void_p), ("ld1", ct.c_int64),
-                    ("out2", ct.c_void_p), ("ld2", ct.c_int64), ("resid", ct.c_void_p), ("ldr", ct.c_int64),
-                    ("gate", ct.c_void_p), ("scat", ct.c_void_p), ("scat_idx", ct.c_void_p), ("scat_row0", ct.c_int64),
-                    ("scat_ld", ct.c_int64), ("scat_n", ct.c_int64), ("row0", ct.c_int64)]
-
-    class Mod(ct.Structure):
-        _fields_ = [("B", ct.c_int32), ("stride", ct.c_int64), ("end", ct.c_int64 * 32)]
-
-    class Args(ct.Structure):
-        _fields_ = [("p", Problem * 2), ("nprob", ct.c_int), ("N", ct.c_int64), ("K", ct.c_int64), ("n_split", ct.c_int64),
-                    ("n_split2", ct.c_int64), ("mode0", ct.c_int), ("mode1", ct.c_int), ("mode2", ct.c_int), ("mod", Mod)]
-
-    out = subprocess.run(["nm", "-D", "--defined-only", avits.lib_path()], capture_output=True, text=True).stdout
-    launch = getattr(ct.CDLL(avits.lib_path()), re.search(r"\bT (_ZN5avits11launch_gemm\w+)", out).group(1))
-    launch.argtypes = [ct.c_void_p, ct.c_int, ct.c_void_p, ct.c_char_p, ct.c_void_p, ct.c_size_t, ct.c_void_p]
-    a = Args(nprob=1, N=64, K=64, n_split=64, n_split2=64, mode0=2)  # EPI_RESID_GATE
+    a = _gemm.Args(nprob=1, N=64, K=64, n_split=64, n_split2=64, mode0=_gemm.RESID_GATE)
     a.p[0].M = 10
     a.mod.B = 2
     for partial in (None, FAKE):
-        assert launch(ct.addressof(a), 0, None, b"gemm_o", partial, 1 << 30 if partial else 0, None) == UNSUPPORTED
+        assert _gemm.launch(a, avits.F32, partial, 1 << 30 if partial else 0) == UNSUPPORTED
         assert b"per-image gates" in lib.avits_last_error()
     a.p[0].M = 0   # nothing to do
-    assert launch(ct.addressof(a), 0, None, b"gemm_o", None, 0, None) == 0
+    assert _gemm.launch(a, avits.F32, None, 0) == 0
+
+
+def test_gemm_plans_off_the_16_byte_grid(lib):
+    # A bias one element off its 16-byte boundary keeps the 256-wide tile, the k
+    # splits and the split tail (the register-staged kernels, `stages` 2).
+    D, scratch = 3072, 4 * 1741 * 3072 * 4   # the block reserves four [S, D] fp32 splits
+
+    def plan(M, N, K, bias=16 + 2):
+        a = _gemm.Args(nprob=1, N=N, K=K, n_split=N, n_split2=N)
+        a.p[0].A = a.p[0].W = a.p[0].out0 = 0x10000
+        a.p[0].bias, a.p[0].M, a.p[0].lda, a.p[0].ld0 = bias, M, K, N
+        r = _gemm.plan(a, avits.BF16, scratch)
+        return r.bn, r.stages, r.splits, r.tail, r.tail_splits
+
+    assert plan(1741, D, D) == (256, 2, 3, 0, 1)            # 84 tiles: 252 units of the 256 CUs
+    assert plan(1741, 3 * D, D) == (256, 2, 1, 0, 1)        # 252 tiles
+    assert plan(1741, 4 * D, D) == (256, 2, 1, 80, 3)       # 336 tiles: the last 80 in three splits
+    assert plan(300, 3 * D, D)[:2] == (256, 2)
+    assert plan(1741, D, D, bias=16)[1] == 1                # on the grid: the ping-pong kernel
+    assert plan(0, D, D)[2:] == (1, 0, 1) and _gemm.launch(_gemm.Args(nprob=1, N=D, K=D), avits.BF16, None, 0) == 0

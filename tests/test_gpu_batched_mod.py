@@ -106,8 +106,9 @@ def test_block_batched_per_image_modulation(gpu, kind):
 
 # Unsplit (the gates in the GEMM's epilogue), in two and three k splits (in the
 # reduce), with every tile or the last one in a split tail (in the tail's
-# reduce), the 128-wide form, and the general kernel.
-GATED_PLANS = ["256,1", "256,2", "256,3", "256,1,8,1,100,2", "256,1,8,1,1,3", "128,1,8,1", "128,2,8,1", "128,1,8,2"]
+# reduce), the 128-wide form, and the register-staged kernels.
+GATED_PLANS = ["256,1", "256,2", "256,3", "256,1,8,1,100,2", "256,1,8,1,1,3", "128,1,8,1", "128,2,8,1", "256,3,8,2",
+               "256,1,8,2,100,2", "128,1,8,2"]
 
 
 @pytest.mark.parametrize("plan", GATED_PLANS)
