@@ -1594,8 +1594,8 @@ GemmPlan plan_gemm(const GemmArgs& a, int dtype, size_t partial_bytes, const cha
     int bn = 0, sp = 0, wv = 8, stg = 0, tail = 0, tsp = 1;
     const int got = sscanf(env, "%d,%d,%d,%d,%d,%d", &bn, &sp, &wv, &stg, &tail, &tsp);
     if (got < 4) stg = bn == 256 ? 1 : 2;
-    if (got >= 2 && (bn == 256 || bn == 192 || bn == 128) && sp >= 1 && sp <= 4 && wv == 8 && (stg == 1 || stg == 2)) {
-      pl.bn = bn == 256 ? 256 : 128;
+    if (got >= 2 && (bn == 256 || bn == 128) && sp >= 1 && sp <= 4 && wv == 8 && (stg == 1 || stg == 2)) {
+      pl.bn = bn;
       pl.stages = wide ? stg : 2;
       pl.splits = sp;
       pl.tiles = tiles_of(a, kBM, pl.bn);

@@ -387,3 +387,21 @@ def test_gemm_plans_off_the_16_byte_grid(lib):
     assert plan(300, 3 * D, D)[:2] == (256, 2)
     assert plan(1741, D, D, bias=16)[1] == 1                # on the grid: the ping-pong kernel
     assert plan(0, D, D)[2:] == (1, 0, 1) and _gemm.launch(_gemm.Args(nprob=1, N=D, K=D), avits.BF16, None, 0) == 0
+
+
+def test_gemm_plan_override(lib, monkeypatch):
+    # Each form names its own kernel (width, `stages`); a width that no kernel has changes nothing.
+    a = _gemm.Args(nprob=1, N=3072, K=3072, n_split=3072, n_split2=3072)
+    a.p[0].M, a.p[0].lda, a.p[0].ld0 = 1741, 3072, 3072
+
+    def plan(text):
+        monkeypatch.setenv("AVITS_GEMM_TILE_gemm", text)
+        r = _gemm.plan(a, avits.BF16, 4 * 1741 * 3072 * 4)
+        return r.bn, r.stages, r.splits, r.tail, r.tail_splits
+
+    assert plan("256,1") == plan("256,1,8,1") == (256, 1, 1, 0, 1)
+    assert plan("128,2,8,1") == (128, 1, 2, 0, 1)
+    assert plan("256,3,8,2") == (256, 2, 3, 0, 1)
+    assert plan("128,1") == plan("128,1,8,2") == (128, 2, 1, 0, 1)
+    assert plan("256,1,8,1,100,3") == (256, 1, 1, 84, 3)
+    assert plan("192,1") == plan("") != plan("128,1")

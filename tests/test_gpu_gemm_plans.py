@@ -1,7 +1,7 @@
 """Every GEMM kernel instance on ragged shapes.  avits_linear (bias, plain
 row-major store) with the plan forced to each unsplit tile form -- the
-256-wide ping-pong kernel, the 192-wide kernel, the 128-wide kernel with one
-and with two register stages -- and the fp32 kernel, on M, N and K that leave
+ping-pong kernel 256 and 128 wide, the register-staged kernels 256 and 128
+wide -- and the fp32 kernels, on M, N and K that leave
 partial row and column tiles, element by element against an fp64 product of
 the same (bf16-rounded) operands.  The bound per element: the products are
 summed in fp32 (at most K roundings of a partial sum no larger than
@@ -14,7 +14,7 @@ import torch
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(1, 8, 64), (255, 136, 128), (257, 264, 192), (600, 520, 448), (1030, 1288, 64)]
-PLANS = ["256,1", "192,1", "128,1,8,1", "128,1,8,2"]
+PLANS = ["256,1", "128,1,8,1", "256,1,8,2", "128,1,8,2"]
 
 
 def _run(gpu, monkeypatch, M, N, K, dtype, plan=None):
