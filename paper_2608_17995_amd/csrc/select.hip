@@ -63,8 +63,9 @@ __global__ __launch_bounds__(kThreads) void radix_select_batched_kernel(const fl
 // cost as much as a launch, one workgroup scans the counts between the two
 // (offsets).  Bound by: launches, up to a few million scores (2^20: 4 MB, under
 // 1 us of memory time): seven, where a launch per digit pick and the offset scan
-// made twelve: N = 2^18 49 -> 38 us, 2^20 54 -> 40, 2^23 115 -> 77, 2^25 252 -> 244.
-// Loads issued four deep in the histogram passes change nothing.
+// made twelve: N = 2^18 50 -> 36 us, 2^20 54 -> 38, 2^23 115 -> 73.  Beyond, by the
+// reads: 2^25 250 -> 198, 2^26 390 -> 356 (six streams of 268 MB and the indices:
+// 4.8 TB/s).
 // Scores are read with 16-byte loads; every pass streams them once.
 constexpr int kGT = 256;               // threads per workgroup of the grid passes
 constexpr int kGWaves = kGT / kWave;
@@ -72,8 +73,10 @@ constexpr int kHT = 1024;              // threads per histogram workgroup
 constexpr int kHWaves = kHT / kWave;
 // Histogram workgroups at most (grid-stride), and keys for each.  Each ends
 // with an atomic per bin, on bins that all share: many small workgroups spend
-// their time there (256 of 256 threads on 2^20 scores: 9 us a pass).
-constexpr int kHistBlocks = 256, kHistKeys = 16 * kHT;
+// their time there (256 of 256 threads on 2^20 scores: 9 us a pass).  At most the
+// two per CU that run at once: with 256 workgroups a CU keeps too few loads in
+// flight (2^26 scores: 10 us more a pass).
+constexpr int kHistBlocks = 512, kHistKeys = 16 * kHT;
 constexpr int kChunk = 16 * kGT;       // elements per count / emit workgroup (16 per thread)
 constexpr int kSumChunks = 2048;       // chunks whose counts the emission sums itself
 
@@ -93,16 +96,11 @@ __global__ __launch_bounds__(kGT) void select_init_kernel(SelState* __restrict__
   }
 }
 
-// State before pass `pass`, by every workgroup of a launch (the first one
+// State before pass `pass` (> 0), by every workgroup of a launch (the first one
 // records it): the digit b of the pass before with (matching keys above b) <
-// need <= (matching keys at or above b).
+// need <= (matching keys at or above b).  The results are in scalar registers.
 __device__ __forceinline__ void select_pick(SelState* __restrict__ st, int pass, uint32_t& prefix, uint32_t& need) {
   __shared__ uint32_t wsum[kGWaves], picked[2];
-  if (pass == 0) {
-    prefix = st->prefix[0];
-    need = st->need[0];
-    return;
-  }
   const int b = threadIdx.x, wave = b / kWave, lane = b % kWave;
   const uint32_t c = b < 256 ? st->hist[pass - 1][b] : 0u, last = st->prefix[pass - 1], rank = st->need[pass - 1];
   const uint32_t suf = wave_incl_suffix_u32(c);  // suffix sum inside the wave, high lanes down
@@ -115,8 +113,8 @@ __device__ __forceinline__ void select_pick(SelState* __restrict__ st, int pass,
     picked[1] = rank - above;
   }
   __syncthreads();
-  prefix = picked[0];
-  need = picked[1];
+  prefix = __builtin_amdgcn_readfirstlane(picked[0]);
+  need = __builtin_amdgcn_readfirstlane(picked[1]);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     st->prefix[pass] = prefix;
     st->need[pass] = need;
@@ -146,6 +144,11 @@ __device__ __forceinline__ void load_keys4(const float* __restrict__ scores, con
 
 constexpr int kSubHist = 2;  // LDS histogram copies per wave (lane % 2): spreads atomics on one bin
 
+// FIRST: pass 0, no prefix to match.  A template, so that the rounds below unroll
+// and every wait for the prefix lies before the loop: as a loop, with a prefix
+// that one path loads, the compiler waited for all loads in every iteration, the
+// prefetched keys among them (2^26 equal scores: 62 us a pass against 51).
+template <bool FIRST>
 __global__ __launch_bounds__(kHT) void select_hist_kernel(const float* __restrict__ scores,
                                                           const float* __restrict__ delta, int64_t N, int pass,
                                                           SelState* __restrict__ st) {
@@ -153,11 +156,11 @@ __global__ __launch_bounds__(kHT) void select_hist_kernel(const float* __restric
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
   uint32_t* h = hs[wave * kSubHist + (lane & (kSubHist - 1))];
   for (int b = tid; b < kHWaves * kSubHist * 256; b += kHT) (&hs[0][0])[b] = 0u;
-  uint32_t prefix, need;
-  select_pick(st, pass, prefix, need);
+  uint32_t prefix = 0u, need;
+  if constexpr (!FIRST) select_pick(st, pass, prefix, need);
   __syncthreads();
   const int shift = 24 - 8 * pass;
-  const uint32_t mask = pass ? 0xffffffffu << (32 - 8 * pass) : 0u;
+  const uint32_t mask = FIRST ? 0u : 0xffffffffu << (32 - 8 * pass);
   // The top digit of similar scores coincides (one exponent covers most of a
   // min-max-normalised score range), so in the first pass a wave adds its two
   // most frequent-looking digits with one atomic each (ballot) before the
@@ -165,7 +168,7 @@ __global__ __launch_bounds__(kHT) void select_hist_kernel(const float* __restric
   // aggregate only one (which also bounds the cost of heavily tied scores).
   // A thread's four keys go through each round together: one leader digit,
   // one ballot per key, one atomic for all of them.
-  const int rounds = pass == 0 ? 2 : 1;
+  constexpr int rounds = FIRST ? 2 : 1;
   auto count4 = [&](const uint32_t (&key)[4], const bool (&ok)[4]) {
     bool pending[4];
     uint32_t digit[4];
@@ -174,6 +177,7 @@ __global__ __launch_bounds__(kHT) void select_hist_kernel(const float* __restric
       pending[e] = ok[e] && (key[e] & mask) == prefix;
       digit[e] = (key[e] >> shift) & 255u;
     }
+#pragma unroll
     for (int it = 0; it < rounds; ++it) {
       const uint64_t act = __ballot(pending[0] || pending[1] || pending[2] || pending[3]);
       if (act == 0) break;
@@ -486,8 +490,9 @@ static int select_impl(const float* scores, const float* delta, int64_t N, int64
   const int hblocks = int(std::min<int64_t>(kHistBlocks, (N + kHistKeys - 1) / kHistKeys));
   TimedLaunch timed("select", s);
   hipLaunchKernelGGL(select_init_kernel, dim3(1), dim3(kGT), 0, s, ws.st, uint32_t(k));
-  for (int pass = 0; pass < 4; ++pass)
-    hipLaunchKernelGGL(select_hist_kernel, dim3(hblocks), dim3(kHT), 0, s, scores, delta, N, pass, ws.st);
+  hipLaunchKernelGGL(select_hist_kernel<true>, dim3(hblocks), dim3(kHT), 0, s, scores, delta, N, 0, ws.st);
+  for (int pass = 1; pass < 4; ++pass)
+    hipLaunchKernelGGL(select_hist_kernel<false>, dim3(hblocks), dim3(kHT), 0, s, scores, delta, N, pass, ws.st);
   hipLaunchKernelGGL(select_count_kernel, dim3(nchunks), dim3(kGT), 0, s, scores, delta, N, ws.st, ws.cnt);
   if (nchunks <= kSumChunks) {
     hipLaunchKernelGGL(select_emit_kernel<true>, dim3(nchunks), dim3(kGT), 0, s, scores, delta, N, ws.st, ws.cnt, k, idx);
