@@ -410,9 +410,9 @@ int avits_block_forward_batched(const void* x_in, void* x_out, const int32_t* po
  * [6, D] (double) or [3, D] (single) blocks out mod_stride elements apart,
  * e.g. as [B, 6, D] with mod_stride = 6 D.  mod_stride == 0 shares one set
  * across the images (exactly avits_block_forward_batched).  Every other
- * weight is shared.  The gated projections apply their per-image gates in
- * their split-K reduce, so they always run split (the workspace of
- * avits_block_workspace_bytes covers it).  Errors as
+ * weight is shared.  The per-image gates are applied wherever the gated
+ * projections' final rows are made (the workspace of
+ * avits_block_workspace_bytes covers every plan).  Errors as
  * avits_block_forward_batched; AVITS_ERR_INVALID_ARG for mod_stride < 0.
  * ---------------------------------------------------------------------- */
 int avits_block_forward_batched_ex(const void* x_in, void* x_out, const int32_t* pos, float pos_scale,

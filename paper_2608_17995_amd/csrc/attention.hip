@@ -8,9 +8,9 @@
 // and S(t + 1) = K Q^T) do not depend on its softmax (of S(t)), so a wave
 // issues them interleaved, in a fixed order: the matrix pipe runs under the
 // exponentials.
-// Bound by: the matrix pipe at the clock that full load leaves (1.65 GHz
-// measured): without the softmax the same loop takes 2.43 ms at S = 16896, 24
-// heads, without fragment reads 2.83, whole 3.15 (1110 TFLOP/s).  Measured
+// Bound by: the matrix pipe at the clock that full load leaves (S = 16896, 24 heads:
+// 1.64 GHz, 62 % busy): without the softmax the same loop takes 2.43 ms there,
+// without fragment reads 2.83, whole 3.15 (1110 TFLOP/s).  Measured
 // before -> now (tiles staged through registers, the softmax between the two
 // products): S = 16896 3.71 -> 3.15 ms, 5171 414 -> 345 us, the masked pass of
 // S = 2457 119 -> 104 us.  On 16x16x32 products, which the GEMM prefers, 3.28 ms:
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const AttnArgs a) {
   typedef f32x16 STile[kKT / 32];
   typedef bf16x8 PTile[kKT / 16];
   constexpr int kQK = kC * (kKT / 32), kPV = WITH_V ? kDT * (kKT / 16) : 0;
-    constexpr int kRd = 4;  // fragments read ahead of their product
+  constexpr int kRd = 4;  // fragments read ahead of their product
   // Slots 0 .. kPV - 1 of a step are the V^T fragments of O^T += V^T P^T (kDT
   // independent chains), the next kQK the K fragments of S = K Q^T (two).  In
   // this order S(t + 1) and P(t) take over registers that S(t) and P(t - 1)

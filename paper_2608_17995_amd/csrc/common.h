@@ -180,7 +180,9 @@ __device__ __forceinline__ void buffer_load16(u32x4& dst, const u32x4& rsrc, uin
 
 // 16-byte-per-lane buffer load that lands in LDS directly: lane l's data goes
 // to LDS byte dst + off + 16 l (dst + off wave-uniform).  No register receives the
-// data; completion is counted by vmcnt like any load.
+// data; completion is counted by vmcnt like any load.  The compiler sees no hazard
+// inside the block: rsrc and soff must not come from a vector instruction within
+// five wait states before it (they pass through scalar arithmetic everywhere).
 __device__ __forceinline__ void lds_load16(uint32_t dst, uint32_t voff, const u32x4& rsrc, uint32_t soff,
                                            uint32_t off = 0) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"

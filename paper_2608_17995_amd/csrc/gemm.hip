@@ -837,8 +837,9 @@ __device__ __forceinline__ uint32_t xcd_logical_id32(uint32_t bid, uint32_t grid
 // phase 2t + 1: every load is issued in a memory phase, each memory phase
 // issues the same eight per wave, and each load has at least two phases
 // (about 2000 cycles) before a barrier that waits for it.
-// Bound by: the clock under full matrix load (1.55 GHz measured, matrix pipe
-// 78 % busy).  Hence the 16x16x32 products: alone, on all CUs, they sustain
+// Bound by: the clock under full matrix load (8192^3: 1.63 GHz, the matrix pipe 84 %
+// busy; 16896 x 12288 x 3072: 1.64 GHz, 72 %; 1741 x 9216 x 3072, which is too short
+// for that: 2.0 GHz, 60 %).  Hence the 16x16x32 products: alone, on all CUs, they sustain
 // 2036 TFLOP/s where 32x32x16 sustain 1806 (a smaller accumulator is read and
 // written per operation).  Measured (bias epilogue, TFLOP/s, before: tiles
 // staged through registers, fragments read between the MFMAs; then on 32x32x16;
