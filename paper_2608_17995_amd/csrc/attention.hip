@@ -9,7 +9,7 @@
 // issues them interleaved, in a fixed order: the matrix pipe runs under the
 // exponentials.
 // Bound by: the matrix pipe at the clock that full load leaves (S = 16896, 24 heads:
-// 1.64 GHz, 62 % busy): without the softmax the same loop takes 2.43 ms there,
+// 1.6-1.7 GHz, 62 % busy): without the softmax the same loop takes 2.43 ms there,
 // without fragment reads 2.83, whole 3.15 (1110 TFLOP/s).  Measured
 // before -> now (tiles staged through registers, the softmax between the two
 // products): S = 16896 3.71 -> 3.15 ms, 5171 414 -> 345 us, the masked pass of

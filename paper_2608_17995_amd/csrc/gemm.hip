@@ -599,8 +599,10 @@ __global__ __launch_bounds__(512) void gemm_bf16_kernel(const GemmArgs a, float*
 // main loop's LDS once every wave is done with it.
 //   acc[i][j][r] = C[row 16 i + l16][col 16 j + 4 g + r], l16 = lane % 16, g = lane / 16.
 // Row-major image: 128-byte rows, 16-byte chunk c of row r at chunk
-// c ^ ((r / 2) mod 8): the 8-byte accumulator writes (16 rows, two halves of a
-// chunk) and the 16-byte row reads are free of bank conflicts.
+// c ^ ((r / 2) mod 8), which spreads the 8-byte accumulator writes (16 rows, two
+// halves of a chunk) and the 16-byte row reads over all banks.  (Counted: none of
+// the main loop's LDS instructions conflicts, the epilogue's 48 per wave lose 2.7
+// cycles each.)
 // Transposed image: 256-byte columns; lanes l, l ^ 1 first exchange half of
 // their four columns, so each holds two rows of two columns and writes
 // 4-byte row pairs; 16-byte chunk k of column c is at k ^ 2 ((c / 2) mod 8)
@@ -837,9 +839,9 @@ __device__ __forceinline__ uint32_t xcd_logical_id32(uint32_t bid, uint32_t grid
 // phase 2t + 1: every load is issued in a memory phase, each memory phase
 // issues the same eight per wave, and each load has at least two phases
 // (about 2000 cycles) before a barrier that waits for it.
-// Bound by: the clock under full matrix load (8192^3: 1.63 GHz, the matrix pipe 84 %
-// busy; 16896 x 12288 x 3072: 1.64 GHz, 72 %; 1741 x 9216 x 3072, which is too short
-// for that: 2.0 GHz, 60 %).  Hence the 16x16x32 products: alone, on all CUs, they sustain
+// Bound by: the clock under full matrix load (8192^3: 1.6-1.7 GHz from box to box,
+// the matrix pipe 84 % busy; 16896 x 12288 x 3072: 1.5 GHz, 76 %; 1741 x 9216 x 3072,
+// which is too short for that: 2.0 GHz, 61 %).  Hence the 16x16x32 products: alone, on all CUs, they sustain
 // 2036 TFLOP/s where 32x32x16 sustain 1806 (a smaller accumulator is read and
 // written per operation).  Measured (bias epilogue, TFLOP/s, before: tiles
 // staged through registers, fragments read between the MFMAs; then on 32x32x16;
