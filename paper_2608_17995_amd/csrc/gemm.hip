@@ -937,20 +937,24 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmArgs args, 
     const u32x4 rw = uniform(buffer_rsrc(W + n0 * K, range32((N - n0) * K * 2)));
     const uint32_t a_dst = lds0 + a_half * 128 + sub * 1024;
     const uint32_t w_dst = lds0 + RA * kA * 16 + w_half * 128 + sub * 1024;
-    // This wave's share of k-tile t of A or W, into a slot of its ring.  Past
-    // the last k-tile the resource's range and the scalar offset are 0: every
+    // This wave's share of k-tile t of A or W, into a slot of its ring (in: t < n_t
+    // for sure).  Past the last k-tile the resource's range and the scalar offset are 0: every
     // offset is out of range (also where the range is taken less the scalar
     // offset, which then may not exceed it), no memory is read, and the loads
     // still count, so every wait below is the same constant.
-    auto load_a = [&](int t, int slot) {
-      const uint32_t koff = t < n_t ? uint32_t(kt0 + t) * (kBK * 2) : 0u;
-      const u32x4 r = {ra[0], ra[1], t < n_t ? ra[2] : 0u, ra[3]};
+    using Sure = std::integral_constant<bool, true>;
+    using Maybe = std::integral_constant<bool, false>;
+    auto load_a = [&](int t, int slot, auto in) {
+      const bool live = decltype(in)::value || t < n_t;
+      const uint32_t koff = live ? uint32_t(kt0 + t) * (kBK * 2) : 0u;
+      const u32x4 r = {ra[0], ra[1], live ? ra[2] : 0u, ra[3]};
 #pragma unroll
       for (int j = 0; j < LA; ++j) lds_load16(a_dst + slot * (kA * 16), a_off[j], r, koff, 4096 * j);
     };
-    auto load_w = [&](int t, int slot) {
-      const uint32_t koff = t < n_t ? uint32_t(kt0 + t) * (kBK * 2) : 0u;
-      const u32x4 r = {rw[0], rw[1], t < n_t ? rw[2] : 0u, rw[3]};
+    auto load_w = [&](int t, int slot, auto in) {
+      const bool live = decltype(in)::value || t < n_t;
+      const uint32_t koff = live ? uint32_t(kt0 + t) * (kBK * 2) : 0u;
+      const u32x4 r = {rw[0], rw[1], live ? rw[2] : 0u, rw[3]};
 #pragma unroll
       for (int j = 0; j < LW; ++j) lds_load16(w_dst + slot * (kW * 16), w_off[j], r, koff, 4096 * j);
     };
@@ -1000,48 +1004,54 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmArgs args, 
     };
     if (here > 0) bar();   // every wave is done with the last unit's epilogue
     if (grp == 0) {
-      load_w(0, 0);
+      load_w(0, 0, Maybe());
 #pragma unroll
       for (int t = 0; t < RA - 1; ++t) {
-        load_a(t, t);
-        load_w(t + 1, t + 1);
+        load_a(t, t, Maybe());
+        load_w(t + 1, t + 1, Maybe());
       }
       vm_wait<(RA - 1) * kStep>();
       bar();
-      for (int t = 0; t < n_t; ++t) {
+      auto step = [&](int t, auto in) {
         read(as, ws);
-        load_a(t + RA - 1, ap);
-        load_w(t + RW - 1, wp);
+        load_a(t + RA - 1, ap, in);
+        load_w(t + RW - 1, wp, in);
         vm_wait<LW + (RA - 1) * kStep>();   // the second half of A(t), which phase 2t + 1 reads
         bar();
         mul();
         vm_wait<(RA - 1) * kStep>();        // the first half of W(t + 1), which phase 2t + 2 reads
         bar();
         next();
-      }
+      };
+      int t = 0;
+      for (; t + RW - 1 < n_t; ++t) step(t, Sure());
+      for (; t < n_t; ++t) step(t, Maybe());
       vm_wait<0>();
       bar();
     } else {
 #pragma unroll
       for (int t = 0; t < RA; ++t) {
-        load_a(t, t);
-        load_w(t, t);
+        load_a(t, t, Maybe());
+        load_w(t, t, Maybe());
       }
       vm_wait<(RA - 1) * kStep>();
       bar();
       if (n_t == 0) vm_wait<0>();
       bar();
-      for (int t = 0; t < n_t; ++t) {
+      auto step = [&](int t, auto in) {
         read(as, ws);
-        load_a(t + RA, as);
-        load_w(t + RW - 1, wp);
+        load_a(t + RA, as, in);
+        load_w(t + RW - 1, wp, in);
         vm_wait<(RA - 1) * kStep>();        // both halves of tile t + 1, which phase 2t + 2 reads
         bar();
         mul();
-        if (t == n_t - 1) vm_wait<0>();
+        if (!decltype(in)::value && t == n_t - 1) vm_wait<0>();
         bar();
         next();
-      }
+      };
+      int t = 0;
+      for (; t + RW - 1 < n_t; ++t) step(t, Sure());
+      for (; t < n_t; ++t) step(t, Maybe());
     }
 
     // Split partials: a tail tile's go to its own 256 x 256 block (split-major),
