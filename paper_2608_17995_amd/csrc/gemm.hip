@@ -838,7 +838,10 @@ __device__ __forceinline__ uint32_t xcd_logical_id32(uint32_t bid, uint32_t grid
 // only, so free after phase 2t) and the second half of W of tile t + 2 in
 // phase 2t + 1: every load is issued in a memory phase, each memory phase
 // issues the same eight per wave, and each load has at least two phases
-// (about 2000 cycles) before a barrier that waits for it.
+// (about 2000 cycles) before a barrier that waits for it.  (As built, the compiler
+// also waits for the loads in flight halfway through a fragment read, because of
+// registers that an epilogue path of the unit before loads; with that wait out of
+// the way nothing was faster, 0.992 to 1.013 over fifteen cases.)
 // Bound by: the clock under full matrix load (8192^3: 1.6-1.7 GHz from box to box,
 // the matrix pipe 84 % busy; 16896 x 12288 x 3072: 1.5 GHz, 76 %; 1741 x 9216 x 3072,
 // which is too short for that: 2.0 GHz, 61 %).  Hence the 16x16x32 products: alone, on all CUs, they sustain
